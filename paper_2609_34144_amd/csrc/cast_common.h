@@ -32,12 +32,12 @@ struct RoutePlan {
   int D;            // H * dh
   int ngrp;         // channel groups of kMeansCh
   int segs;         // n_a + M pooled rows
-  size_t off_means, total;
+  size_t off_means, off_scores, total;   // scores [n_a, H, M]: only above kOneLaunchM chunks
 };
 constexpr int kMeansWaves = 8;      // waves per pooled-mean block
 constexpr int kMeansCh = 128;       // channels per pooled-mean block (16 lanes x 8 bf16)
-constexpr int kRankMaxM = 256;      // TopK by counting larger keys up to this many chunks
-constexpr int kRouteMaxM = 4096;    // bitonic keys live in 32 KB of LDS
+constexpr int kOneLaunchM = 512;      // scores and TopK in one launch up to this many chunks
+constexpr int kRouteMaxM = 4096;    // four keys per thread of the selection's 16 waves
 
 RoutePlan plan_route(int n_a, int S, int H, int dh, int M, int Bv);
 

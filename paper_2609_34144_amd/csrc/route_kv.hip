@@ -6,10 +6,12 @@
 //              means q_bar, k_bar.
 // route_topk   one block per (anchor, head): scores s = scale * q_bar . k_bar for
 //              all M chunks, then the k_eff best under (score descending, chunk index
-//              ascending), written in ascending chunk order: by counting larger keys
-//              for up to kRankMaxM chunks, by bitonic sorts in LDS above.
+//              ascending), written in ascending chunk order.  Above kOneLaunchM chunks
+//              the scores (route_scores) and the selection (route_select) are two
+//              launches.
 // No atomics anywhere: results are bit-identical across runs.
 #include "cast_common.h"
+#include "topk_select.h"
 
 namespace cast {
 
@@ -90,125 +92,112 @@ __global__ __launch_bounds__(kMeansWaves * 64) void route_means_kernel(
   }
 }
 
-// In-LDS bitonic sort of P (power of two) 64-bit keys into descending order.
-__device__ void bitonic_desc(unsigned long long* key, int P) {
-  for (int kk = 2; kk <= P; kk <<= 1) {
-    for (int j = kk >> 1; j > 0; j >>= 1) {
-      for (int x = threadIdx.x; x < P; x += blockDim.x) {
-        const int y = x ^ j;
-        if (y > x) {
-          const unsigned long long a = key[x], b = key[y];
-          const bool desc = (x & kk) == 0;
-          if (desc ? (a < b) : (a > b)) { key[x] = b; key[y] = a; }
-        }
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// Score key of chunk m: ordered float bits (monotone in s), then the inverted chunk
-// index, so a larger key is a better chunk and ties go to the lower index.
-__device__ __forceinline__ unsigned long long score_key(float s, int m) {
-  uint32_t b = __float_as_uint(s);
-  if ((b << 1) == 0u) b = 0u;   // -0 and +0 compare equal: give them one key
-  const uint32_t ord = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-  return ((unsigned long long)ord << 32) | (uint32_t)(~(uint32_t)m);
-}
-
-// One block of 256 threads per (anchor i, head h).  Scores: wave w takes chunks
-// m = w, w + 4, ..., four at a time; each lane multiplies its dims of q_bar and
-// k_bar_m and the wave sums the products by lane exchanges (fixed order).  With
-// M <= kRankMaxM the selection counts, for every chunk, the keys larger than its
-// own (no sort): chunk m is kept when fewer than k_eff are larger, and its output
-// slot is the number of kept chunks below m (ascending chunk order).  Larger M
-// sorts the keys with two bitonic passes in LDS.
-template <int DH>
+// Up to kOneLaunchM chunks: one block of four waves per (anchor i, head h) scores its
+// chunks 64 at a time (score_tile, no barrier between the tiles) and its first wave
+// selects (topk_words on one wave, KPT keys per lane): one launch, whose latency is
+// what counts at this size.  KPT is the smallest that holds the chunks (8 keys per
+// lane cost 100 chunks 1.1 us over 4).  The call at 200 chunks of 64 tokens: 34.3 us
+// with a lane exchange per four chunks and a rank count over all keys, now 20.5.
+template <int DH, int KPT>
 __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict__ means, int n_a,
-                                                         int H, int M, int P, int k_eff, float scale,
+                                                         int H, int M, int k_eff, float scale,
                                                          float* __restrict__ scores_out,
                                                          int32_t* __restrict__ idx_out) {
-  extern __shared__ unsigned long long keys[];
-  __shared__ unsigned long long kept[kRankMaxM / 64];
-  constexpr int PER = DH / 64 > 0 ? DH / 64 : 1;       // dims per lane
+  __shared__ float sc[KPT * 64];
+  __shared__ sel::Scratch scratch;
   const int i = blockIdx.x / H, h = blockIdx.x - (blockIdx.x / H) * H;
   const int D = H * DH;
+  for (int m0 = 0; m0 < M; m0 += sel::kScoreBlock)
+    sel::score_tile<DH, 1>(means, n_a, M, D, h, i, m0, scale, sc + m0, 0);
+  __syncthreads();
+  if (scores_out)
+    for (int m = threadIdx.x; m < M; m += 256) scores_out[((long long)i * H + h) * M + m] = sc[m];
+  if (threadIdx.x >= 64) return;
+  uint32_t key[KPT];
+  bool valid[KPT];
+  unsigned long long win[KPT];
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    const int m = j * 64 + threadIdx.x;
+    valid[j] = m < M;
+    key[j] = valid[j] ? sel::order_key(sc[m]) : 0u;
+  }
+  int par = 0;
+  sel::topk_words<1, KPT>(key, valid, k_eff, scratch, par, win);
+  sel::write_indices<1, KPT>(win, scratch, par, idx_out + ((long long)i * H + h) * k_eff);
+}
+
+// More chunks: the scores come from a launch of their own, whose grid (head, 64
+// chunks, four anchors) reads every k_bar row once per four anchors from all
+// compute units, and one 16-wave block per (anchor, head) selects.  Bound by launch
+// and load latency: 1760 chunks, 4 anchors, 24 heads of 128 take 16 us for both
+// launches (one block per (anchor, head) that scored four chunks per wave at a time
+// and sorted the keys in LDS took 266 us).  The line at kOneLaunchM: 512 chunks run
+// 35.2 us a call in one launch and 38.9 in two (24 heads of 128), 300 chunks 18.4
+// and 22.9; past it the one block's scoring loop grows by about 2 us per 64 chunks.
+template <int DH>
+__global__ __launch_bounds__(256) void route_scores_kernel(const float* __restrict__ means, int n_a,
+                                                           int H, int M, float scale,
+                                                           float* __restrict__ scores,
+                                                           float* __restrict__ scores_out) {
+  __shared__ float tile[4 * sel::kScoreBlock];
+  const int h = blockIdx.x, m0 = blockIdx.y * sel::kScoreBlock, i0 = blockIdx.z * 4;
+  const int na = min(4, n_a - i0);
+  sel::score_tile<DH, 4>(means, n_a, M, H * DH, h, i0, m0, scale, tile, sel::kScoreBlock);
+  __syncthreads();
+  const int ii = threadIdx.x >> 6, m = m0 + (threadIdx.x & 63);
+  if (ii < na && m < M) {
+    const long long o = ((long long)(i0 + ii) * H + h) * M + m;
+    const float v = tile[threadIdx.x];
+    scores[o] = v;
+    if (scores_out) scores_out[o] = v;
+  }
+}
+
+constexpr int kSelectWaves = 16;
+template <int KPT>
+__global__ __launch_bounds__(kSelectWaves * 64) void route_select_kernel(
+    const float* __restrict__ scores, int M, int k_eff, int32_t* __restrict__ idx_out) {
+  __shared__ sel::Scratch scratch;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float qv[PER];
+  const float* s = scores + (long long)blockIdx.x * M;
+  uint32_t key[KPT];
+  bool valid[KPT];
+  unsigned long long win[KPT];
 #pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int d = lane * PER + e;
-    qv[e] = d < DH ? means[(long long)i * D + h * DH + d] : 0.0f;
+  for (int j = 0; j < KPT; ++j) {
+    const int m = (wave * KPT + j) * 64 + lane;
+    valid[j] = m < M;
+    key[j] = valid[j] ? sel::order_key(s[m]) : 0u;
   }
-  for (int m0 = wave * 4; m0 < M; m0 += 16) {
-    float part[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int m = m0 + u;
-      part[u] = 0.0f;
-      if (m < M) {
-        const float* kr = means + (long long)(n_a + m) * D + h * DH;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-          const int d = lane * PER + e;
-          if (d < DH) part[u] = fmaf(qv[e], kr[d], part[u]);
-        }
-      }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) part[u] += __shfl_xor(part[u], o);
-    if (lane < 4 && m0 + lane < M) {
-      const int m = m0 + lane;
-      const float sc = (lane == 0 ? part[0] : lane == 1 ? part[1] : lane == 2 ? part[2] : part[3]) * scale;
-      if (scores_out) scores_out[((long long)i * H + h) * M + m] = sc;
-      keys[m] = score_key(sc, m);
-    }
+  int par = 0;
+  sel::topk_words<kSelectWaves, KPT>(key, valid, k_eff, scratch, par, win);
+  sel::write_indices<kSelectWaves, KPT>(win, scratch, par, idx_out + (long long)blockIdx.x * k_eff);
+}
+
+template <int DH>
+cast_status_t launch_topk(const float* means, int n_a, int H, int M, int k_eff, float scale,
+                          float* scores_out, int32_t* idx_out, float* scores, hipStream_t stream) {
+  if (M <= kOneLaunchM) {
+    const auto fn = M <= 64 ? route_topk_kernel<DH, 1>
+                            : (M <= 256 ? route_topk_kernel<DH, 4> : route_topk_kernel<DH, kOneLaunchM / 64>);
+    hipLaunchKernelGGL(fn, dim3(n_a * H), dim3(256), 0, stream, means, n_a, H, M, k_eff, scale,
+                       scores_out, idx_out);
+    return check_launch("route_topk");
   }
-  int32_t* dst = idx_out + ((long long)i * H + h) * k_eff;
-  if (M <= kRankMaxM) {
-    __syncthreads();
-    for (int m = threadIdx.x; m - (int)(threadIdx.x & 63) < M; m += blockDim.x) {
-      bool keep = false;
-      if (m < M) {
-        const unsigned long long mine = keys[m];
-        int rank = 0;
-        for (int x = 0; x < M; ++x) rank += keys[x] > mine ? 1 : 0;
-        keep = rank < k_eff;
-      }
-      const unsigned long long mask = __ballot(keep);
-      if ((threadIdx.x & 63) == 0) kept[m >> 6] = mask;
-    }
-    __syncthreads();
-    for (int m = threadIdx.x; m < M; m += blockDim.x) {
-      const unsigned long long own = kept[m >> 6];
-      if ((own >> (m & 63)) & 1ull) {
-        int pos = __popcll(own & ((1ull << (m & 63)) - 1ull));
-        for (int g = 0; g < (m >> 6); ++g) pos += __popcll(kept[g]);
-        dst[pos] = m;
-      }
-    }
-    return;
-  }
-  for (int m = M + threadIdx.x; m < P; m += blockDim.x) keys[m] = 0ull;
-  __syncthreads();
-  bitonic_desc(keys, P);
-  // the k_eff best, re-keyed so that a descending sort lists them by ascending index
-  for (int x = threadIdx.x; x < P; x += blockDim.x) {
-    unsigned long long k2 = 0ull;
-    if (x < k_eff) {
-      const uint32_t m = ~(uint32_t)(keys[x] & 0xffffffffull);
-      k2 = (unsigned long long)(~m);
-    }
-    keys[x] = k2;
-  }
-  __syncthreads();
-  bitonic_desc(keys, P);
-  for (int x = threadIdx.x; x < k_eff; x += blockDim.x) {
-    uint32_t m = ~(uint32_t)(keys[x] & 0xffffffffull);
-    dst[x] = (int32_t)(m < (uint32_t)M ? m : (uint32_t)(M - 1));
-  }
+  hipLaunchKernelGGL(route_scores_kernel<DH>,
+                     dim3(H, (M + sel::kScoreBlock - 1) / sel::kScoreBlock, (n_a + 3) / 4), dim3(256), 0,
+                     stream, means, n_a, H, M, scale, scores, scores_out);
+  cast_status_t st = check_launch("route_scores");
+  if (st != CAST_OK) return st;
+  const dim3 grid(n_a * H), block(kSelectWaves * 64);
+  if (M <= kSelectWaves * 64)
+    hipLaunchKernelGGL(route_select_kernel<1>, grid, block, 0, stream, scores, M, k_eff, idx_out);
+  else if (M <= kSelectWaves * 128)
+    hipLaunchKernelGGL(route_select_kernel<2>, grid, block, 0, stream, scores, M, k_eff, idx_out);
+  else
+    hipLaunchKernelGGL(route_select_kernel<4>, grid, block, 0, stream, scores, M, k_eff, idx_out);
+  return check_launch("route_select");
 }
 
 }  // namespace
@@ -221,7 +210,8 @@ RoutePlan plan_route(int n_a, int S, int H, int dh, int M, int Bv) {
   p.ngrp = (p.D + kMeansCh - 1) / kMeansCh;
   p.segs = n_a + M;
   p.off_means = 0;
-  p.total = align_up((size_t)p.segs * p.D * sizeof(float));
+  p.off_scores = align_up((size_t)p.segs * p.D * sizeof(float));
+  p.total = p.off_scores + (M > kOneLaunchM ? align_up((size_t)n_a * H * M * sizeof(float)) : 0);
   return p;
 }
 
@@ -240,24 +230,12 @@ cast_status_t launch_route(const void* q, const void* k, int n_a, int S, int H, 
   float* means = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_means);
   cast_status_t st = launch_pool_means(q, k, n_a, S, M, Bv, p, means, stream);
   if (st != CAST_OK) return st;
-  int P = 2;
-  while (P < M) P <<= 1;
-  const size_t shm = (size_t)(P > 64 ? P : 64) * sizeof(unsigned long long);
+  float* scores = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_scores);
   switch (dh) {
-    case 32:
-      hipLaunchKernelGGL(route_topk_kernel<32>, dim3(n_a * H), dim3(256), shm, stream, means, n_a, H,
-                         M, P, k_eff, scale, scores_out, idx_out);
-      break;
-    case 64:
-      hipLaunchKernelGGL(route_topk_kernel<64>, dim3(n_a * H), dim3(256), shm, stream, means, n_a, H,
-                         M, P, k_eff, scale, scores_out, idx_out);
-      break;
-    default:
-      hipLaunchKernelGGL(route_topk_kernel<128>, dim3(n_a * H), dim3(256), shm, stream, means, n_a, H,
-                         M, P, k_eff, scale, scores_out, idx_out);
-      break;
+    case 32: return launch_topk<32>(means, n_a, H, M, k_eff, scale, scores_out, idx_out, scores, stream);
+    case 64: return launch_topk<64>(means, n_a, H, M, k_eff, scale, scores_out, idx_out, scores, stream);
+    default: return launch_topk<128>(means, n_a, H, M, k_eff, scale, scores_out, idx_out, scores, stream);
   }
-  return check_launch("route_topk");
 }
 
 }  // namespace cast

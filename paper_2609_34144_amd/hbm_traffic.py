@@ -29,7 +29,7 @@ COPY_BYTES = 1 << 29          # 512 MiB fp32 copy: larger than the Infinity Cach
 COPY_KERNEL = "__amd_rocclr_copyBuffer"   # the HIP runtime's device-to-device copy
 CALIB_REPS = 3
 KERNEL_SOURCES = {
-    "route": ["route_kv.hip"],
+    "route": ["route_kv.hip", "topk_select.h"],
     "attn": ["anchor_attn.hip"],
     "par": ["par.hip", "par_device.h", "par_fused.hip", "fft_tile.h"],
 }
