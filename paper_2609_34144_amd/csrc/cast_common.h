@@ -30,7 +30,6 @@ __device__ __forceinline__ float bf16hi(uint32_t w) { return __uint_as_float(w &
 // ---------------------------------------------------------------------------
 struct RoutePlan {
   int D;            // H * dh
-  int ngrp;         // channel groups of kMeansCh
   int segs;         // n_a + M pooled rows
   size_t off_means, off_scores, total;   // scores [n_a, H, M]: only above kOneLaunchM chunks
 };
@@ -41,10 +40,10 @@ constexpr int kRouteMaxM = 4096;    // four keys per thread of the selection's 1
 
 RoutePlan plan_route(int n_a, int S, int H, int dh, int M, int Bv);
 
-// Pooled means of n_a frames of q (S tokens) and M chunks of k (Bv tokens):
-// means [n_a + M, D] fp32 (q_bar rows first).  n_a may be 0.
-cast_status_t launch_pool_means(const void* q, const void* k, int n_a, int S, int M, int Bv,
-                                const RoutePlan& p, float* means, hipStream_t stream);
+// Pooled means of n_a frames of q (S tokens), M chunks of k and, with v, M chunks of
+// v (Bv tokens): means [n_a + M (+ M), D] fp32 (rows q_bar, k_bar, v_bar).
+cast_status_t launch_pool_means(const void* q, const void* k, const void* v, int n_a, int S, int M,
+                                int Bv, int D, float* means, hipStream_t stream);
 
 cast_status_t launch_route(const void* q, const void* k, int n_a, int S, int H, int dh, int M,
                            int Bv, int k_eff, float scale, float* scores_out, int32_t* idx_out,
@@ -57,8 +56,8 @@ constexpr int kCoupledMaxAnchors = 512;
 constexpr int kCoupledMaxMask = 32768;   // n_a * M retain flags held in LDS by the solver
 
 struct CoupledPlan {
-  RoutePlan qk, v;      // pooled-mean scans of (Q, K) and of V
-  size_t off_means_qk, off_means_v, off_u, total;
+  int n_split;          // score workgroups along the chunks, one part of o_bar each
+  size_t off_means, off_scores, off_part, off_u, total;
 };
 CoupledPlan plan_coupled(int n_a, int S, int H, int dh, int M, int Bv);
 

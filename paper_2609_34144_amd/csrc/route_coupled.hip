@@ -2,201 +2,231 @@
 // eq:omission, eq:abc, eq:risk, eq:objective, eq:topk; App. B eq:abcclosed,
 // eq:boundarycoeff, eq:gain, eq:boundarygain, Algorithm 1).
 //
-// route_means (route_kv.hip)   token means of Q and K, then of V
-// coupled_omission  grid (anchor x head, range of 16 blocks): scores over the M
-//                   blocks, softmax, o_bar, then for each block of the range
-//                   u = (pi/(1-pi+eps))^2 d^T G_h d with d = o_bar - v_bar[m]
-//                   (G_h = P_h^T P_h, so ||P_h d||^2 costs dh^2, not D dh)
+// route_means (route_kv.hip)   token means of Q, K and V in one launch
+// coupled_scores    grid (head, 64 chunks, four anchors): the scores of the tile
+//                   and, per anchor, the tile's softmax maximum and sum and its part
+//                   of o_bar (unnormalised), which the next launch merges
+// coupled_omission  grid (anchor x head, 32 to 128 chunks): o_bar from the parts, then for
+//                   each chunk of the range u = (pi/(1-pi+eps))^2 d^T G_h d with
+//                   d = o_bar - v_bar[m] (G_h = P_h^T P_h, so ||P_h d||^2 costs dh^2,
+//                   not D dh)
 // coupled_refine    one workgroup per head (heads never interact): masks start as
-//                   TopK(u), then Algorithm 1's directional passes; every TopK is a
-//                   bitonic sort of 64-bit keys (ordered value bits, inverted block
-//                   index) in LDS; the head's objective J is kept up to date by the
+//                   TopK(u), then Algorithm 1's directional passes; every lane keeps
+//                   its chunks' values in registers and the TopK counts them down
+//                   (topk_select.h); the head's objective J is kept up to date by the
 //                   accepted gain differences
 // wo_gram           G_h from the bf16 output projection (weights only, once per model)
 // All reductions run in a fixed order and nothing is atomic: results are
 // bit-identical across runs.
 #include "cast_common.h"
+#include "topk_select.h"
 
 namespace cast {
 
 namespace {
 
-constexpr int kOmM = 16;          // blocks per omission workgroup (4 per wave)
 constexpr int kThreads = 256;
-constexpr int kRefineThreads = 64;   // the solver runs in one wave per head
-constexpr int kRefineCacheU = 8192;  // u of one head (n_a * M floats) staged in LDS up to this
+// chunks per omission workgroup: its four waves hold dh / 32 row blocks of G times
+// 32 chunks each
+constexpr int om_chunks(int dh) { return 32 * 4 / (dh / 32); }
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+// LDS the solver may take besides its static 5 KB: with room, u of the head and its
+// square roots (2 n_a M floats) are staged beside the masks
+constexpr size_t kRefineLds = 59 * 1024;
 
 struct CoupledArgs {
-  const float* means_qk;   // [n_a + M, D]: q_bar rows, then k_bar rows
-  const float* means_v;    // [M, D]
+  const float* means;      // [n_a + 2 M, D]: q_bar rows, then k_bar rows, then v_bar rows
   const float* gram;       // [H, dh, dh]
+  float* scores;           // [n_a, H, M] (workspace)
+  float* part;             // [n_a, H, n_split, dh + 2]: o_bar part, maximum, sum
   float* u;                // [n_a, H, M] (workspace)
   float* u_out;            // optional copy of u
   int32_t* idx_out;        // [n_a, H, k_eff]
-  int n_a, H, M, D, k_eff, n_frames, passes;
+  int n_a, H, M, D, k_eff, n_frames, passes, n_split;
   float scale, l_anc, l_rec, tol, eps;
   short anchors[kCoupledMaxAnchors];
 };
 
-// Sum of one value per thread of the workgroup, in a fixed order; every thread
-// gets the result.  `red` holds kThreads floats; the call contains barriers.
-__device__ float block_sum(float v, float* red) {
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  const float r = red[0];
-  __syncthreads();
-  return r;
+// Sum over the 64 lanes of a wave, the same on every lane, in a fixed order: row
+// shifts and row broadcasts (DPP adds: no LDS round trip per step, which in the
+// solver's serial chain cost as much as the rest of a step), lane 63 holds the total.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS,
+                                                                   0xf, true));
 }
-
-// Sum over the 64 lanes of a wave by a fixed butterfly: every lane gets the same
-// (order-independent of the schedule) result.
 __device__ __forceinline__ float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = dpp_add<0x111, 0xf>(v);   // row_shr:1
+  v = dpp_add<0x112, 0xf>(v);   // row_shr:2
+  v = dpp_add<0x114, 0xf>(v);   // row_shr:4
+  v = dpp_add<0x118, 0xf>(v);   // row_shr:8: lane 15 of each row holds the row's sum
+  v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+__device__ __forceinline__ float wave_max(float v) {
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
   return v;
 }
 
-__device__ float block_max(float v, float* red) {
-  red[threadIdx.x] = v;
+// ---------------------------------------------------------------------------
+// scores, softmax parts and o_bar parts (eq:pooled)
+// ---------------------------------------------------------------------------
+// Every k_bar and v_bar row is read once per four anchors, and the grid fills the
+// chip (24 heads x 28 tiles at 1760 chunks); scoring all chunks again in every
+// omission workgroup took 134 us at 390 chunks, 3 anchors and 12 heads of 128.
+template <int DH>
+__global__ __launch_bounds__(kThreads) void coupled_scores_kernel(CoupledArgs a) {
+  constexpr int NP = kThreads / DH;              // parts of the tile's chunks in o_bar
+  constexpr int CP = sel::kScoreBlock / NP;      // chunks per part
+  __shared__ float tile[4 * sel::kScoreBlock];
+  __shared__ float red[NP][4][DH];
+  const int h = blockIdx.x, sp = blockIdx.y, m0 = sp * sel::kScoreBlock, i0 = blockIdx.z * 4;
+  const int na = min(4, a.n_a - i0), nm = min(sel::kScoreBlock, a.M - m0);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  sel::score_tile<DH, 4>(a.means, a.n_a, a.M, a.D, h, i0, m0, a.scale, tile, sel::kScoreBlock);
   __syncthreads();
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
+  // wave w takes anchor i0 + w: maximum, unnormalised probabilities and their sum
+  if (wave < na) {
+    const long long ih = (long long)(i0 + wave) * a.H + h;
+    const float sc = tile[tid];
+    const bool in = lane < nm;
+    if (in) a.scores[ih * a.M + m0 + lane] = sc;
+    const float mx = wave_max(in ? sc : -INFINITY);
+    const float e = in ? expf(sc - mx) : 0.0f;
+    const float sum = wave_sum(e);
+    tile[tid] = e;
+    if (lane == 0) {
+      float* p = a.part + (ih * a.n_split + sp) * (DH + 2) + DH;
+      p[0] = mx;
+      p[1] = sum;
+    }
   }
-  const float r = red[0];
   __syncthreads();
-  return r;
+  // thread -> (channel, part of the chunks), all four anchors; parts in a fixed order
+  {
+    const int d = tid % DH, part = tid / DH;
+    const float* v = a.means + (long long)(a.n_a + a.M + m0) * a.D + h * DH + d;
+    const int c0 = part * CP, c1 = min(c0 + CP, nm);
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 8
+    for (int c = c0; c < c1; ++c) {
+      const float x = v[(long long)c * a.D];
+#pragma unroll
+      for (int ii = 0; ii < 4; ++ii) acc[ii] = fmaf(tile[ii * sel::kScoreBlock + c], x, acc[ii]);
+    }
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii) red[part][ii][d] = acc[ii];
+  }
+  __syncthreads();
+  for (int x = tid; x < na * DH; x += kThreads) {
+    const int ii = x / DH, d = x - ii * DH;
+    float o = 0.0f;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) o += red[p][ii][d];
+    a.part[(((long long)(i0 + ii) * a.H + h) * a.n_split + sp) * (DH + 2) + d] = o;
+  }
 }
 
 // ---------------------------------------------------------------------------
-// omission proxy u (eq:pooled, eq:omission)
+// omission proxy u (eq:omission)
 // ---------------------------------------------------------------------------
+// y = G d for the range's difference vectors on the matrix cores in fp32
+// (v_mfma_f32_32x32x2_f32, exact products and fp32 accumulation): wave w takes 32 rows
+// of G (by symmetry its columns, so the loads coalesce) and 32 vectors, one vector per
+// lane column, so d . y is the lane's own sum.  Its G operand (DH floats per lane) is
+// loaded whole at the start, in flight during the o_bar merge.  Bound by that load and
+// the launch at few chunks, by the fp32 MFMA rate at many.
 template <int DH>
 __global__ __launch_bounds__(kThreads) void coupled_omission_kernel(CoupledArgs a) {
-  extern __shared__ float sm[];
-  float* e = sm;               // [M] scores, then unnormalised probabilities
-  float* qs = e + a.M;         // [DH]
-  float* ob = qs + DH;         // [DH]
-  float* red = ob + DH;        // [kThreads]
-  float* dv = red + kThreads;  // [kOmM][DH] difference vectors, kOmM / 4 per wave
-  const int ih = blockIdx.x, i = ih / a.H, h = ih - (ih / a.H) * a.H;
-  const int m0 = blockIdx.y * kOmM;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  for (int d = tid; d < DH; d += kThreads) qs[d] = a.means_qk[(long long)i * a.D + h * DH + d];
-  __syncthreads();
-  // scores: one wave per block, lanes over the channels
-  float lmax = -INFINITY;
-  for (int m = wave; m < a.M; m += kThreads / 64) {
-    const float* kb = a.means_qk + (long long)(a.n_a + m) * a.D + h * DH;
-    float s = 0.0f;
-    for (int d = lane; d < DH; d += 64) s = fmaf(qs[d], kb[d], s);
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    s *= a.scale;
-    if (lane == 0) e[m] = s;
-    lmax = fmaxf(lmax, s);
-  }
-  __syncthreads();
-  const float smax = block_max(lmax, red);
-  float lsum = 0.0f;
-  for (int m = tid; m < a.M; m += kThreads) {
-    const float x = expf(e[m] - smax);
-    e[m] = x;
-    lsum += x;
-  }
-  const float ssum = block_sum(lsum, red);
-  // o_bar = sum_m pi_m v_bar_m: thread -> (channel, part of the blocks), parts
-  // combined in a fixed order
+  constexpr int RB = DH / 32;                    // 32-row blocks of G
+  constexpr int NV = om_chunks(DH);              // vectors (chunks) of the workgroup
+  constexpr int NP = kThreads / DH;
+  constexpr int DS = NV + 4;                     // row stride of the transposed vectors
+  constexpr int kMaxSplit = kRouteMaxM / sel::kScoreBlock;
+  __shared__ float dt[DH * DS];                  // dt[c][vector]
+  __shared__ float ob[DH], red[NP][DH], fac[kMaxSplit], norm[2], quad[RB][NV];
+  const int ih = blockIdx.x, h = ih % a.H;
+  const int m0 = blockIdx.y * NV;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l32 = lane & 31, hf = lane >> 5;
+  const int r0 = (wave % RB) * 32, v0 = (wave / RB) * 32;
+  // operand A of MFMA step t: row r0 + l32, column 2 t + hf
+  float g[DH / 2];
   {
-    constexpr int NP = kThreads / DH;
-    const int d = tid % DH, part = tid / DH;
-    float acc = 0.0f;
-    for (int m = part; m < a.M; m += NP)
-      acc = fmaf(e[m], a.means_v[(long long)m * a.D + h * DH + d], acc);
-    red[tid] = acc;
-    __syncthreads();
-    if (tid < DH) {
-      float o = 0.0f;
-      for (int p = 0; p < NP; ++p) o += red[p * DH + tid];
-      ob[tid] = o / ssum;
-    }
-    __syncthreads();
-  }
-  // u for the blocks of this range: wave w takes the 4 blocks m0 + 4w .. +3 at
-  // once, so every G element loaded serves 4 difference vectors
-  constexpr int MW = kOmM / 4;
-  const float* G = a.gram + (long long)h * DH * DH;   // symmetric: row l of column c = G[c][l]
-  float* dw = dv + wave * MW * DH;                    // [MW][DH]
-  const int mw0 = m0 + MW * wave;
+    const float* G = a.gram + (long long)h * DH * DH + hf * DH + r0 + l32;
 #pragma unroll
-  for (int j = 0; j < MW; ++j) {
-    const int m = min(mw0 + j, a.M - 1);
-    for (int c = lane; c < DH; c += 64) dw[j * DH + c] = ob[c] - a.means_v[(long long)m * a.D + h * DH + c];
+    for (int t = 0; t < DH / 2; ++t) g[t] = G[2 * t * DH];
+  }
+  const float* part = a.part + (long long)ih * a.n_split * (DH + 2);
+  // o_bar from the tiles' parts: weights exp(max_s - max) over the sum of all
+  if (wave == 0) {
+    const bool in = lane < a.n_split;
+    const float mx = in ? part[lane * (DH + 2) + DH] : -INFINITY;
+    const float sm = in ? part[lane * (DH + 2) + DH + 1] : 0.0f;
+    const float smax = wave_max(mx);
+    const float f = in ? expf(mx - smax) : 0.0f;
+    const float ssum = wave_sum(f * sm);
+    fac[lane] = f;
+    if (lane == 0) {
+      norm[0] = smax;
+      norm[1] = ssum;
+    }
   }
   __syncthreads();
-  float y1[MW], y2[MW];
-#pragma unroll
-  for (int j = 0; j < MW; ++j) { y1[j] = 0.0f; y2[j] = 0.0f; }
-  const int l1 = lane < DH ? lane : 0;
+  {
+    const int d = tid % DH, p = tid / DH;
+    float acc = 0.0f;
 #pragma unroll 4
-  for (int c = 0; c < DH; ++c) {
-    const float g1 = G[c * DH + l1];
-    const float g2 = DH > 64 ? G[c * DH + lane + 64] : 0.0f;
-#pragma unroll
-    for (int j = 0; j < MW; ++j) {
-      const float dc = dw[j * DH + c];
-      y1[j] = fmaf(g1, dc, y1[j]);
-      if (DH > 64) y2[j] = fmaf(g2, dc, y2[j]);
-    }
+    for (int s = p; s < a.n_split; s += NP) acc = fmaf(fac[s], part[s * (DH + 2) + d], acc);
+    red[p][d] = acc;
   }
+  __syncthreads();
+  const float smax = norm[0], ssum = norm[1];
+  if (tid < DH) {
+    float o = 0.0f;
 #pragma unroll
-  for (int j = 0; j < MW; ++j) {
-    const int m = mw0 + j;
-    float part = lane < DH ? dw[j * DH + lane] * y1[j] : 0.0f;
-    if (DH > 64) part += dw[j * DH + lane + 64] * y2[j];
-    for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
-    if (m < a.M && lane == 0) {
-      const float pi = e[m] / ssum;
-      const float cf = pi / (1.0f - pi + a.eps);
-      const float u = cf * cf * part;
-      const long long o = ((long long)i * a.H + h) * a.M + m;
-      a.u[o] = u;
-      if (a.u_out) a.u_out[o] = u;
-    }
+    for (int p = 0; p < NP; ++p) o += red[p][tid];
+    ob[tid] = o / ssum;
+  }
+  __syncthreads();
+  const float* vm = a.means + (long long)(a.n_a + a.M) * a.D + h * DH;
+#pragma unroll 8
+  for (int x = tid; x < NV * DH; x += kThreads) {
+    const int j = x / DH, c = x - j * DH;
+    dt[c * DS + j] = ob[c] - vm[(long long)min(m0 + j, a.M - 1) * a.D + c];
+  }
+  __syncthreads();
+  const float* dv = dt + v0 + l32;               // this lane's vector
+  f32x16 y{};
+#pragma unroll
+  for (int t = 0; t < DH / 2; ++t)
+    y = __builtin_amdgcn_mfma_f32_32x32x2f32(g[t], dv[(2 * t + hf) * DS], y, 0, 0, 0);
+  // element e of the accumulator: row r0 + 8 (e / 4) + 4 hf + e % 4, the lane's vector
+  float qs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int e = 0; e < 16; ++e) qs[e % 4] = fmaf(dv[(r0 + 8 * (e / 4) + 4 * hf + e % 4) * DS], y[e], qs[e % 4]);
+  float q = (qs[0] + qs[1]) + (qs[2] + qs[3]);
+  q += __shfl_xor(q, 32);
+  if (hf == 0) quad[wave % RB][v0 + l32] = q;
+  __syncthreads();
+  const int m = m0 + tid;
+  if (tid < NV && m < a.M) {
+    float d2 = 0.0f;
+#pragma unroll
+    for (int r = 0; r < RB; ++r) d2 += quad[r][tid];
+    const long long o = (long long)ih * a.M + m;
+    const float pi = expf(a.scores[o] - smax) / ssum;
+    const float cf = pi / (1.0f - pi + a.eps);
+    const float u = cf * cf * d2;
+    a.u[o] = u;
+    if (a.u_out) a.u_out[o] = u;
   }
 }
 
 // ---------------------------------------------------------------------------
 // Algorithm 1 (eq:gain, eq:boundarygain, eq:topk)
 // ---------------------------------------------------------------------------
-// In-LDS bitonic sort of P (power of two) 64-bit keys into descending order by
-// the nthr threads of the workgroup.
-__device__ void bitonic_desc(unsigned long long* key, int P, int nthr) {
-  for (int kk = 2; kk <= P; kk <<= 1) {
-    for (int j = kk >> 1; j > 0; j >>= 1) {
-      for (int x = threadIdx.x; x < P; x += nthr) {
-        const int y = x ^ j;
-        if (y > x) {
-          const unsigned long long p = key[x], q = key[y];
-          const bool desc = (x & kk) == 0;
-          if (desc ? (p < q) : (p > q)) { key[x] = q; key[y] = p; }
-        }
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// 64-bit key of value v of block m: larger v first, then lower m.
-__device__ __forceinline__ unsigned long long order_key(float v, int m) {
-  uint32_t b = __float_as_uint(v);
-  if ((b << 1) == 0u) b = 0u;   // -0 and +0 compare equal
-  const uint32_t ord = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-  return ((unsigned long long)ord << 32) | (uint32_t)(~(uint32_t)m);
-}
-
 struct Coeffs {
   // interval (rows j, j+1): A = B, C from the closed form of eq:abcclosed
   // boundary sides (eq:boundarycoeff): rows (ra, rb) and sums over their frames
@@ -204,38 +234,59 @@ struct Coeffs {
   float al, bl, cl, ar, br, cr;
 };
 
-// One wave per head: the solver is a chain of small sorts and sums, and with a
-// single wave every barrier is immediate and every sum a shuffle butterfly.
-template <bool CACHE_U>
-__global__ __launch_bounds__(kRefineThreads) void coupled_refine_kernel(CoupledArgs a) {
-  extern __shared__ unsigned long long keys[];        // [P]
+// The solver is a serial chain of small selections and sums, bound by latency.  Lane
+// l, slot j of wave w owns chunk m = ((w KPT) + j) 64 + l of every row, so gains,
+// masks (one 64-bit word per row and slot) and u are touched only by their owner and
+// the waves meet only in the sums and the selection's counts (refine_for chooses how
+// many; a single wave runs without a barrier).  (Sorting the keys in LDS and editing the
+// masks from one lane took 589 us at 390 chunks, 3 anchors, 78 kept; 52 us at 32
+// chunks and 4 anchors.)
+template <int NW, int KPT, bool CACHE_U>
+__global__ __launch_bounds__(NW * 64) void coupled_refine_kernel(CoupledArgs a) {
+  extern __shared__ unsigned long long xm[];          // [n_a][NW * KPT] retain words
+  constexpr int WORDS = NW * KPT;
   const int M = a.M, n_a = a.n_a, k = a.k_eff, h = blockIdx.x;
-  int P = 2;
-  while (P < M) P <<= 1;
-  float* g = reinterpret_cast<float*>(keys + P);      // [M] gains of the visited row
-  uint32_t* xm = reinterpret_cast<uint32_t*>(g + M);  // [n_a * M] retain bits
-  const int nwords = (n_a * M + 31) / 32;
-  float* su = reinterpret_cast<float*>(xm + nwords);  // [n_a * M] u of this head (CACHE_U)
+  float* su = reinterpret_cast<float*>(xm + n_a * WORDS);   // [n_a][M] u of this head (CACHE_U)
+  float* sq = su + (CACHE_U ? n_a * M : 0);                 // its square roots
   __shared__ Coeffs cf;
   __shared__ float pair_ab[kCoupledMaxAnchors], pair_c[kCoupledMaxAnchors];
-  const int tid = threadIdx.x;
-  // u is read at every step of the solver: staged in LDS when it fits
+  __shared__ sel::Scratch scratch;
+  const int tid = threadIdx.x, lane = tid & 63, wave = NW == 1 ? 0 : tid >> 6;
+  const int mb = wave * KPT * 64 + lane;              // this lane's chunks: mb + 64 j
+  // slots past the last chunk read it and are masked out, so that a row's loads are
+  // all in flight together
+  bool valid[KPT];
+  int mc[KPT];
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    valid[j] = mb + 64 * j < M;
+    mc[j] = min(mb + 64 * j, M - 1);
+  }
+  const float* gu = a.u + (long long)h * M;
+  const long long urow = (long long)a.H * M;
   if constexpr (CACHE_U)
-    for (int x = tid; x < n_a * M; x += kRefineThreads) {
-      const int i = x / M, m = x - (x / M) * M;
-      su[x] = a.u[((long long)i * a.H + h) * M + m];
-    }
-  auto U = [&](int i, int m) -> float {
-    if constexpr (CACHE_U) return su[i * M + m];
-    else return a.u[((long long)i * a.H + h) * M + m];
+    for (int i = 0; i < n_a; ++i)
+#pragma unroll
+      for (int j = 0; j < KPT; ++j)
+        if (valid[j]) {
+          const float x = gu[i * urow + mc[j]];
+          su[i * M + mc[j]] = x;
+          sq[i * M + mc[j]] = sqrtf(x);
+        }
+  auto U = [&](int i, int j) -> float {
+    if constexpr (CACHE_U) return su[i * M + mc[j]];
+    else return gu[i * urow + mc[j]];
   };
-  auto X = [&](int i, int m) -> float {
-    const int bit = i * M + m;
-    return (xm[bit >> 5] >> (bit & 31)) & 1u ? 1.0f : 0.0f;
+  auto R = [&](int i, int j) -> float {
+    if constexpr (CACHE_U) return sq[i * M + mc[j]];
+    else return sqrtf(gu[i * urow + mc[j]]);
+  };
+  auto X = [&](int i, int j) -> float {
+    return (xm[i * WORDS + wave * KPT + j] >> lane) & 1ull ? 1.0f : 0.0f;
   };
 
   // ---- coefficients
-  for (int j = tid; j + 1 < n_a; j += kRefineThreads) {
+  for (int j = tid; j + 1 < n_a; j += NW * 64) {
     const float n = (float)(a.anchors[j + 1] - a.anchors[j]);
     pair_ab[j] = (n - 1.0f) * (2.0f * n - 1.0f) / (6.0f * n);
     pair_c[j] = (n * n - 1.0f) / (6.0f * n);
@@ -262,106 +313,102 @@ __global__ __launch_bounds__(kRefineThreads) void coupled_refine_kernel(CoupledA
     }
     cf = c;
   }
-  for (int w = tid; w < nwords; w += kRefineThreads) xm[w] = 0u;
-  __syncthreads();
+  sel::clear_scratch(scratch);
 
-  // TopK of the values in g[0..M): leaves the winners first in keys[], returns
-  // their sum (the same on every thread)
-  auto topk_sum = [&]() -> float {
-    if (M <= kRefineThreads) {
-      // one value per lane: its rank is the number of larger keys (the keys are
-      // distinct, so the ranks are too); the winners are stored in rank order
-      const bool in = tid < M;
-      const float gv = in ? g[tid] : 0.0f;
-      const unsigned long long km = in ? order_key(gv, tid) : 0ull;
-      int rank = 0;
-      for (int j = 0; j < M; ++j) rank += __shfl(km, j) > km ? 1 : 0;
-      const bool win = in && rank < k;
-      if (win) keys[rank] = km;
-      return wave_sum(win ? gv : 0.0f);
+  int par = 0;
+  // sums of two values over the workgroup, the same on every thread
+  auto group_sum2 = [&](float& x, float& y) {
+    x = wave_sum(x);
+    y = wave_sum(y);
+    if constexpr (NW > 1) {
+      if (lane == 0) {
+        scratch.sum[par & 1][wave][0] = x;
+        scratch.sum[par & 1][wave][1] = y;
+      }
+      __syncthreads();
+      x = scratch.sum[par & 1][lane % NW][0];
+      y = scratch.sum[par & 1][lane % NW][1];
+#pragma unroll
+      for (int o = NW / 2; o > 0; o >>= 1) {
+        x += __shfl_xor(x, o);
+        y += __shfl_xor(y, o);
+      }
+      if (tid == 0) scratch.cnt[(par + 2) & 3] = 0ull;   // (keeps the ring's turn)
+      ++par;
     }
-    for (int m = tid; m < P; m += kRefineThreads) keys[m] = m < M ? order_key(g[m], m) : 0ull;
-    __syncthreads();
-    bitonic_desc(keys, P, kRefineThreads);
-    float s = 0.0f;
-    for (int x = tid; x < k; x += kRefineThreads) s += g[~(uint32_t)(keys[x] & 0xffffffffull)];
-    return wave_sum(s);
   };
-  // row i's mask := the k winners left in keys[]
-  auto apply_topk = [&](int i) {
-    const int b0 = i * M, b1 = b0 + M;
-    for (int w = (b0 >> 5) + tid; w <= ((b1 - 1) >> 5); w += kRefineThreads) {   // one owner per word
-      uint32_t word = xm[w];
-      for (int bb = 0; bb < 32; ++bb) {
-        const int bit = (w << 5) + bb;
-        if (bit >= b0 && bit < b1) word &= ~(1u << bb);
-      }
-      xm[w] = word;
+  auto store_words = [&](int i, const unsigned long long (&win)[KPT]) {
+    if (lane == 0) {
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) xm[i * WORDS + wave * KPT + j] = win[j];
     }
-    __syncthreads();
-    if (tid == 0) {
-      for (int x = 0; x < k; ++x) {
-        const int bit = b0 + (int)~(uint32_t)(keys[x] & 0xffffffffull);
-        xm[bit >> 5] |= 1u << (bit & 31);
-      }
-    }
-    __syncthreads();
+    // the owner wave alone reads these words back
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   };
 
   // ---- initial masks: TopK(u) per anchor
+  uint32_t key[KPT];
+  unsigned long long win[KPT];
   for (int i = 0; i < n_a; ++i) {
-    for (int m = tid; m < M; m += kRefineThreads) g[m] = U(i, m);
-    __syncthreads();
-    topk_sum();
-    apply_topk(i);
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) key[j] = valid[j] ? sel::order_key(U(i, j)) : 0u;
+    sel::topk_words<NW, KPT>(key, valid, k, scratch, par, win);
+    store_words(i, win);
   }
 
   // ---- objective J of the head (eq:objective with eq:risk and eq:boundaryrisk)
-  auto risk = [&](int ra, int rb, float A, float B, float C, int m) -> float {
-    const float ua = U(ra, m), ub = U(rb, m), oa = 1.0f - X(ra, m), ob = 1.0f - X(rb, m);
-    return A * oa * ua + B * ob * ub + 2.0f * C * oa * ob * sqrtf(ua) * sqrtf(ub);
+  auto risk = [&](int ra, int rb, float A, float B, float C, int j) -> float {
+    const float oa = 1.0f - X(ra, j), ob = 1.0f - X(rb, j);
+    return A * oa * U(ra, j) + B * ob * U(rb, j) + 2.0f * C * oa * ob * R(ra, j) * R(rb, j);
   };
-  float jpart = 0.0f;
-  for (int m = tid; m < M; m += kRefineThreads) {
-    float anc = 0.0f, rec = 0.0f;
-    for (int i = 0; i < n_a; ++i) anc += (1.0f - X(i, m)) * U(i, m);
-    for (int j = 0; j + 1 < n_a; ++j) rec += risk(j, j + 1, pair_ab[j], pair_ab[j], pair_c[j], m);
-    if (cf.has_l) rec += risk(0, 1, cf.al, cf.bl, cf.cl, m);
-    if (cf.has_r) rec += risk(n_a - 2, n_a - 1, cf.ar, cf.br, cf.cr, m);
-    jpart += a.l_anc * anc + a.l_rec * rec;
+  float J = 0.0f;
+  {
+    float unused = 0.0f;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+      float anc = 0.0f, rec = 0.0f;
+      for (int i = 0; i < n_a; ++i) anc += (1.0f - X(i, j)) * U(i, j);
+      for (int p = 0; p + 1 < n_a; ++p) rec += risk(p, p + 1, pair_ab[p], pair_ab[p], pair_c[p], j);
+      if (cf.has_l) rec += risk(0, 1, cf.al, cf.bl, cf.cl, j);
+      if (cf.has_r) rec += risk(n_a - 2, n_a - 1, cf.ar, cf.br, cf.cr, j);
+      J += valid[j] ? a.l_anc * anc + a.l_rec * rec : 0.0f;
+    }
+    group_sum2(J, unused);
   }
-  float J = wave_sum(jpart);
 
   // ---- directional passes
   for (int s = 0; s < a.passes && k < M; ++s) {
     bool changed = false;
     for (int v = 0; v < n_a; ++v) {
       const int i = (s % 2 == 0) ? v : n_a - 1 - v;
-      float oldpart = 0.0f;
-      for (int m = tid; m < M; m += kRefineThreads) {
-        const float ui = U(i, m), si = sqrtf(ui);
-        float G = a.l_anc * ui, rec = 0.0f;
-        if (i > 0)
-          rec += pair_ab[i - 1] * ui + 2.0f * pair_c[i - 1] * (1.0f - X(i - 1, m)) * sqrtf(U(i - 1, m)) * si;
-        if (i + 1 < n_a)
-          rec += pair_ab[i] * ui + 2.0f * pair_c[i] * (1.0f - X(i + 1, m)) * si * sqrtf(U(i + 1, m));
+      float g[KPT];
+      float g_old = 0.0f, g_new = 0.0f;
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) {
+        const float ui = U(i, j), si = R(i, j);
+        float rec = 0.0f;
+        if (i > 0) rec += pair_ab[i - 1] * ui + 2.0f * pair_c[i - 1] * (1.0f - X(i - 1, j)) * R(i - 1, j) * si;
+        if (i + 1 < n_a) rec += pair_ab[i] * ui + 2.0f * pair_c[i] * (1.0f - X(i + 1, j)) * si * R(i + 1, j);
         if (cf.has_l) {
-          if (i == 0) rec += cf.al * ui + 2.0f * cf.cl * (1.0f - X(1, m)) * si * sqrtf(U(1, m));
-          if (i == 1) rec += cf.bl * ui + 2.0f * cf.cl * (1.0f - X(0, m)) * si * sqrtf(U(0, m));
+          if (i == 0) rec += cf.al * ui + 2.0f * cf.cl * (1.0f - X(1, j)) * si * R(1, j);
+          if (i == 1) rec += cf.bl * ui + 2.0f * cf.cl * (1.0f - X(0, j)) * si * R(0, j);
         }
         if (cf.has_r) {
-          if (i == n_a - 2) rec += cf.ar * ui + 2.0f * cf.cr * (1.0f - X(n_a - 1, m)) * si * sqrtf(U(n_a - 1, m));
-          if (i == n_a - 1) rec += cf.br * ui + 2.0f * cf.cr * (1.0f - X(n_a - 2, m)) * si * sqrtf(U(n_a - 2, m));
+          if (i == n_a - 2) rec += cf.ar * ui + 2.0f * cf.cr * (1.0f - X(n_a - 1, j)) * si * R(n_a - 1, j);
+          if (i == n_a - 1) rec += cf.br * ui + 2.0f * cf.cr * (1.0f - X(n_a - 2, j)) * si * R(n_a - 2, j);
         }
-        G += a.l_rec * rec;
-        g[m] = G;
-        oldpart += X(i, m) * G;
+        g[j] = a.l_anc * ui + a.l_rec * rec;
+        key[j] = valid[j] ? sel::order_key(g[j]) : 0u;
+        g_old += (xm[i * WORDS + wave * KPT + j] >> lane) & 1ull ? g[j] : 0.0f;
       }
-      const float g_old = wave_sum(oldpart);
-      const float g_new = topk_sum();
+      sel::topk_words<NW, KPT>(key, valid, k, scratch, par, win);
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) g_new += (win[j] >> lane) & 1ull ? g[j] : 0.0f;
+      group_sum2(g_old, g_new);
       const float gain = g_new - g_old;
       if (gain > a.tol * fmaxf(J, 1e-8f)) {   // uniform: every thread holds the same sums
-        apply_topk(i);
+        store_words(i, win);
         J -= gain;
         changed = true;
       }
@@ -370,14 +417,33 @@ __global__ __launch_bounds__(kRefineThreads) void coupled_refine_kernel(CoupledA
   }
 
   // ---- ascending block indices of every mask
-  if (tid == 0) {
-    for (int i = 0; i < n_a; ++i) {
-      int32_t* dst = a.idx_out + ((long long)i * a.H + h) * k;
-      int r = 0;
-      for (int m = 0; m < M && r < k; ++m)
-        if (X(i, m) != 0.0f) dst[r++] = m;
-    }
+  for (int i = 0; i < n_a; ++i) {
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) win[j] = xm[i * WORDS + wave * KPT + j];
+    sel::write_indices<NW, KPT>(win, scratch, par, a.idx_out + ((long long)i * a.H + h) * k);
   }
+}
+
+typedef void (*RefineFn)(CoupledArgs);
+template <int NW, int KPT>
+RefineFn refine_fn(bool cache_u, int& waves, int& words) {
+  waves = NW;
+  words = NW * KPT;
+  return cache_u ? coupled_refine_kernel<NW, KPT, true> : coupled_refine_kernel<NW, KPT, false>;
+}
+// The solver of M chunks.  Up to 128 chunks one wave (100 chunks, 3 anchors: 18 us,
+// four waves 24); to 512 four waves of one or two chunks per lane (390 chunks, 78 kept,
+// 3 anchors: 31 us, one wave with eight per lane 45); above, eight waves (1760 chunks,
+// 352 kept, 4 anchors: 74 us, sixteen waves 76).
+RefineFn refine_for(int M, bool cache_u, int& waves, int& words) {
+  if (M <= 64) return refine_fn<1, 1>(cache_u, waves, words);
+  if (M <= 128) return refine_fn<1, 2>(cache_u, waves, words);
+  if (M <= 256) return refine_fn<4, 1>(cache_u, waves, words);
+  if (M <= 512) return refine_fn<4, 2>(cache_u, waves, words);
+  if (M <= 1024) return refine_fn<8, 2>(cache_u, waves, words);
+  if (M <= 2048) return refine_fn<8, 4>(cache_u, waves, words);
+  static_assert(kRouteMaxM <= 8 * 8 * 64, "the largest solver holds every chunk");
+  return refine_fn<8, 8>(cache_u, waves, words);
 }
 
 // ---------------------------------------------------------------------------
@@ -418,14 +484,16 @@ __global__ __launch_bounds__(kThreads) void wo_gram_kernel(const uint16_t* __res
 }  // namespace
 
 CoupledPlan plan_coupled(int n_a, int S, int H, int dh, int M, int Bv) {
+  (void)S;
+  (void)Bv;
   CoupledPlan p{};
-  p.qk = plan_route(n_a, S, H, dh, M, Bv);
-  p.v = plan_route(0, S, H, dh, M, Bv);
-  const size_t D = (size_t)H * dh;
-  p.off_means_qk = 0;
-  p.off_means_v = p.off_means_qk + align_up((size_t)(n_a + M) * D * sizeof(float));
-  p.off_u = p.off_means_v + align_up((size_t)M * D * sizeof(float));
-  p.total = p.off_u + align_up((size_t)n_a * H * M * sizeof(float));
+  const size_t D = (size_t)H * dh, rows = (size_t)n_a * H;
+  p.n_split = (M + sel::kScoreBlock - 1) / sel::kScoreBlock;
+  p.off_means = 0;
+  p.off_scores = align_up((n_a + 2 * (size_t)M) * D * sizeof(float));
+  p.off_part = p.off_scores + align_up(rows * M * sizeof(float));
+  p.off_u = p.off_part + align_up(rows * p.n_split * (dh + 2) * sizeof(float));
+  p.total = p.off_u + align_up(rows * M * sizeof(float));
   return p;
 }
 
@@ -436,9 +504,12 @@ cast_status_t launch_coupled(const void* q, const void* k, const void* v, const 
                              hipStream_t stream) {
   char* base = static_cast<char*>(ws);
   CoupledArgs a{};
-  a.means_qk = reinterpret_cast<float*>(base + p.off_means_qk);
-  a.means_v = reinterpret_cast<float*>(base + p.off_means_v);
+  float* means = reinterpret_cast<float*>(base + p.off_means);
+  a.means = means;
   a.gram = gram;
+  a.scores = reinterpret_cast<float*>(base + p.off_scores);
+  a.part = reinterpret_cast<float*>(base + p.off_part);
+  a.n_split = p.n_split;
   a.u = reinterpret_cast<float*>(base + p.off_u);
   a.u_out = u_out;
   a.idx_out = idx_out;
@@ -455,28 +526,32 @@ cast_status_t launch_coupled(const void* q, const void* k, const void* v, const 
   a.tol = prm.tol;
   a.eps = prm.eps;
   for (int j = 0; j < n_a; ++j) a.anchors[j] = (short)anchors[j];
-  cast_status_t st = launch_pool_means(q, k, n_a, S, M, Bv, p.qk,
-                                       const_cast<float*>(a.means_qk), stream);
+  cast_status_t st = launch_pool_means(q, k, v, n_a, S, M, Bv, a.D, means, stream);
   if (st != CAST_OK) return st;
-  st = launch_pool_means(v, v, 0, S, M, Bv, p.v, const_cast<float*>(a.means_v), stream);
-  if (st != CAST_OK) return st;
-  const dim3 grid(n_a * H, (M + kOmM - 1) / kOmM);
-  const size_t shm = (size_t)(M + 2 * dh + kThreads + kOmM * dh) * sizeof(float);
+  const dim3 sgrid(H, p.n_split, (n_a + 3) / 4);
+  const dim3 ogrid(n_a * H, (M + om_chunks(dh) - 1) / om_chunks(dh));
   switch (dh) {
-    case 32: hipLaunchKernelGGL(coupled_omission_kernel<32>, grid, dim3(kThreads), shm, stream, a); break;
-    case 64: hipLaunchKernelGGL(coupled_omission_kernel<64>, grid, dim3(kThreads), shm, stream, a); break;
-    default: hipLaunchKernelGGL(coupled_omission_kernel<128>, grid, dim3(kThreads), shm, stream, a); break;
+    case 32:
+      hipLaunchKernelGGL(coupled_scores_kernel<32>, sgrid, dim3(kThreads), 0, stream, a);
+      hipLaunchKernelGGL(coupled_omission_kernel<32>, ogrid, dim3(kThreads), 0, stream, a);
+      break;
+    case 64:
+      hipLaunchKernelGGL(coupled_scores_kernel<64>, sgrid, dim3(kThreads), 0, stream, a);
+      hipLaunchKernelGGL(coupled_omission_kernel<64>, ogrid, dim3(kThreads), 0, stream, a);
+      break;
+    default:
+      hipLaunchKernelGGL(coupled_scores_kernel<128>, sgrid, dim3(kThreads), 0, stream, a);
+      hipLaunchKernelGGL(coupled_omission_kernel<128>, ogrid, dim3(kThreads), 0, stream, a);
+      break;
   }
   st = check_launch("coupled_omission");
   if (st != CAST_OK) return st;
-  int P = 2;
-  while (P < M) P <<= 1;
-  const size_t shm2 = (size_t)P * 8 + (size_t)M * 4 + (size_t)((n_a * M + 31) / 32) * 4;
-  if (n_a * M <= kRefineCacheU)
-    hipLaunchKernelGGL(coupled_refine_kernel<true>, dim3(H), dim3(kRefineThreads),
-                       shm2 + (size_t)n_a * M * 4, stream, a);
-  else
-    hipLaunchKernelGGL(coupled_refine_kernel<false>, dim3(H), dim3(kRefineThreads), shm2, stream, a);
+  int waves = 0, words = 0;
+  RefineFn fn = refine_for(M, true, waves, words);
+  size_t shm = (size_t)n_a * words * 8;
+  if (shm + (size_t)n_a * M * 8 <= kRefineLds) shm += (size_t)n_a * M * 8;
+  else fn = refine_for(M, false, waves, words);
+  hipLaunchKernelGGL(fn, dim3(H), dim3(waves * 64), shm, stream, a);
   return check_launch("coupled_refine");
 }
 

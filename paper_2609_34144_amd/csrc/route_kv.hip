@@ -20,15 +20,15 @@ namespace {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // One block per (channel group of kMeansCh channels, segment); segment s < n_a is
-// anchor frame s of q (S tokens), the others are the history chunks of k (Bv
-// tokens).  Wave w sums tokens [w T / 8, (w + 1) T / 8) of the segment: its lane
+// anchor frame s of q (S tokens), the others are the history chunks of k, then (in
+// coupled routing) those of v (Bv tokens).  Wave w sums tokens [w T / 8, (w + 1) T / 8) of the segment: its lane
 // (row r = lane / 16, column = lane % 16) adds 8 consecutive bf16 channels of the
 // tokens t = r mod 4, so one load instruction reads 4 tokens x 256 contiguous
 // bytes, eight of them in flight.  The 4 rows are summed by two lane exchanges,
 // the 8 waves through LDS in wave order: a fixed order, so runs are bit-identical.
 __global__ __launch_bounds__(kMeansWaves * 64) void route_means_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int n_a, int S, int Bv,
-    int D, float* __restrict__ means) {
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    int n_a, int M, int S, int Bv, int D, float* __restrict__ means) {
   __shared__ float red[kMeansWaves][kMeansCh];
   const int grp = blockIdx.x, seg = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -40,7 +40,8 @@ __global__ __launch_bounds__(kMeansWaves * 64) void route_means_kernel(
     base = q + (long long)seg * S * D;
     T = S;
   } else {
-    base = k + (long long)(seg - n_a) * Bv * D;
+    const int m = seg - n_a;
+    base = m < M ? k + (long long)m * Bv * D : v + (long long)(m - M) * Bv * D;
     T = Bv;
   }
   const int t0 = (int)((long long)T * wave / kMeansWaves);
@@ -171,6 +172,7 @@ __global__ __launch_bounds__(kSelectWaves * 64) void route_select_kernel(
     key[j] = valid[j] ? sel::order_key(s[m]) : 0u;
   }
   int par = 0;
+  sel::clear_scratch(scratch);
   sel::topk_words<kSelectWaves, KPT>(key, valid, k_eff, scratch, par, win);
   sel::write_indices<kSelectWaves, KPT>(win, scratch, par, idx_out + (long long)blockIdx.x * k_eff);
 }
@@ -207,7 +209,6 @@ RoutePlan plan_route(int n_a, int S, int H, int dh, int M, int Bv) {
   (void)Bv;
   RoutePlan p{};
   p.D = H * dh;
-  p.ngrp = (p.D + kMeansCh - 1) / kMeansCh;
   p.segs = n_a + M;
   p.off_means = 0;
   p.off_scores = align_up((size_t)p.segs * p.D * sizeof(float));
@@ -215,12 +216,12 @@ RoutePlan plan_route(int n_a, int S, int H, int dh, int M, int Bv) {
   return p;
 }
 
-cast_status_t launch_pool_means(const void* q, const void* k, int n_a, int S, int M, int Bv,
-                                const RoutePlan& p, float* means, hipStream_t stream) {
-  if (p.segs <= 0) return CAST_OK;
-  hipLaunchKernelGGL(route_means_kernel, dim3(p.ngrp, n_a + M), dim3(kMeansWaves * 64), 0, stream,
-                     static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), n_a, S, Bv,
-                     p.D, means);
+cast_status_t launch_pool_means(const void* q, const void* k, const void* v, int n_a, int S, int M,
+                                int Bv, int D, float* means, hipStream_t stream) {
+  const int segs = n_a + M + (v != nullptr ? M : 0);
+  hipLaunchKernelGGL(route_means_kernel, dim3((D + kMeansCh - 1) / kMeansCh, segs), dim3(kMeansWaves * 64),
+                     0, stream, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
+                     static_cast<const uint16_t*>(v), n_a, M, S, Bv, D, means);
   return check_launch("route_means");
 }
 
@@ -228,7 +229,7 @@ cast_status_t launch_route(const void* q, const void* k, int n_a, int S, int H, 
                            int Bv, int k_eff, float scale, float* scores_out, int32_t* idx_out,
                            const RoutePlan& p, void* ws, hipStream_t stream) {
   float* means = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_means);
-  cast_status_t st = launch_pool_means(q, k, n_a, S, M, Bv, p, means, stream);
+  cast_status_t st = launch_pool_means(q, k, nullptr, n_a, S, M, Bv, p.D, means, stream);
   if (st != CAST_OK) return st;
   float* scores = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_scores);
   switch (dh) {

@@ -26,12 +26,18 @@ __device__ __forceinline__ uint32_t order_key(float v) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// LDS scratch of one group (NW > 1 only).
+// LDS scratch of one group (NW > 1 only; clear_scratch before first use).  cnt is a
+// ring of four packed-count slots: a step adds into slot r, meets at a barrier and
+// reads it, and clears slot r + 2, which every wave has read before that barrier.
 struct Scratch {
-  unsigned long long cnt[2][16];
+  unsigned long long cnt[4];
   float sum[2][16][2];
   int word[2][16];
 };
+__device__ __forceinline__ void clear_scratch(Scratch& s) {
+  if (threadIdx.x < 4) s.cnt[threadIdx.x] = 0ull;
+  __syncthreads();
+}
 
 template <int KPT>
 __device__ __forceinline__ int count_ge(const uint32_t (&key)[KPT], uint32_t c) {
@@ -49,22 +55,24 @@ __device__ __forceinline__ void wave_prefix(int mine, Scratch& s, int& par, int&
     total = mine;
   } else {
     const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) s.word[par][wave] = mine;
+    if ((threadIdx.x & 63) == 0) s.word[par & 1][wave] = mine;
     __syncthreads();
     before = total = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const int c = s.word[par][w];
+      const int c = s.word[par & 1][w];
       before += w < wave ? c : 0;
       total += c;
     }
-    par ^= 1;
+    if (threadIdx.x == 0) s.cnt[(par + 2) & 3] = 0ull;   // (keeps the ring's turn)
+    ++par;
   }
 }
 
 // Winner words of this wave's slots: win[j] bit l set when the value at (wave, j, l)
 // is among the k largest.  Slots past the n values carry key 0 and valid = false;
-// 1 <= k <= n.  `par` alternates the LDS buffers (start at 0, keep across calls).
+// 1 <= k <= n.  `par` counts the group's exchanges, which take their LDS
+// buffers by it (start at 0, keep across calls).
 template <int NW, int KPT>
 __device__ __forceinline__ void topk_words(const uint32_t (&key)[KPT], const bool (&valid)[KPT], int k,
                                            Scratch& s, int& par, unsigned long long (&win)[KPT]) {
@@ -79,18 +87,18 @@ __device__ __forceinline__ void topk_words(const uint32_t (&key)[KPT], const boo
       exact = n == k;
     }
   } else {
-    const int wave = threadIdx.x >> 6;
     for (int b = 30; b >= 0 && !exact; b -= 2) {
       const uint32_t c1 = t | (1u << b), c2 = t | (2u << b), c3 = t | (3u << b);
       const unsigned long long mine = (unsigned long long)count_ge(key, c1) |
                                       ((unsigned long long)count_ge(key, c2) << 16) |
                                       ((unsigned long long)count_ge(key, c3) << 32);
-      if ((threadIdx.x & 63) == 0) s.cnt[par][wave] = mine;
+      // one integer add per wave, one read: 16 waves that each read 16 counts would
+      // hold the LDS for longer than the rest of the step takes
+      if ((threadIdx.x & 63) == 0) atomicAdd(&s.cnt[par & 3], mine);
       __syncthreads();
-      unsigned long long all = 0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) all += s.cnt[par][w];
-      par ^= 1;
+      const unsigned long long all = s.cnt[par & 3];
+      if (threadIdx.x == 0) s.cnt[(par + 2) & 3] = 0ull;
+      ++par;
       const int n1 = (int)(all & 0xffff), n2 = (int)((all >> 16) & 0xffff), n3 = (int)(all >> 32);
       if (n3 >= k) t = c3;
       else if (n2 >= k) t = c2;
@@ -176,14 +184,14 @@ __device__ __forceinline__ void score_tile(const float* __restrict__ means, int 
     float v[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-      float a = q0[ii].x * k0[it].x;
+      float a = q0[ii].x * k0[it].x, b = q1[ii].x * k1[it].x;   // two chains, then pairwise
       a = fmaf(q0[ii].y, k0[it].y, a);
+      b = fmaf(q1[ii].y, k1[it].y, b);
       a = fmaf(q0[ii].z, k0[it].z, a);
+      b = fmaf(q1[ii].z, k1[it].z, b);
       a = fmaf(q0[ii].w, k0[it].w, a);
-      a = fmaf(q1[ii].x, k1[it].x, a);
-      a = fmaf(q1[ii].y, k1[it].y, a);
-      a = fmaf(q1[ii].z, k1[it].z, a);
-      v[it] = fmaf(q1[ii].w, k1[it].w, a);
+      b = fmaf(q1[ii].w, k1[it].w, b);
+      v[it] = a + b;
     }
 #pragma unroll
     for (int o = LPC / 2; o > 0; o >>= 1)

@@ -1,0 +1,39 @@
+"""Coupled routing at the edges of its solvers (one wave up to 128 chunks, four to 512,
+eight above; 1, 2, 4 or 8 chunks per lane; u staged in LDS or read from memory) and of
+the omission launch (32, 64 and 128 chunks per workgroup), with the checker and the bars
+of test_gpu_coupled: u against float64, masks exact on heads with a decision margin."""
+import pytest
+
+from gen import workloads as W
+import gen
+from test_gpu_coupled import run_case
+
+pytestmark = pytest.mark.gpu
+
+
+def _workload(H, dh, anchors):
+    return W.Workload(**{**gen.get(W.TINY).__dict__, "H": H, "dh": dh, "anchors": tuple(anchors)})
+
+
+@pytest.mark.parametrize("M", [1, 2, 63, 64, 65, 127, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096])
+def test_solver_edges(cast_lib, M):
+    w = _workload(2, 32, (1, 4, 6))
+    (exact, loose), idx = run_case(cast_lib, w, w.anchors, 9, max(1, M // 6), M=M, Bv=2, seed=M)
+    assert exact + loose == w.H
+    assert (idx[..., 1:] > idx[..., :-1]).all() and int(idx.max()) < M and int(idx.min()) >= 0
+
+
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("M", [31, 33, 97, 130])
+def test_omission_edges(cast_lib, dh, M):
+    w = _workload(3, dh, (0, 2, 3, 5, 8))
+    (exact, loose), _ = run_case(cast_lib, w, w.anchors, 11, max(1, M // 4), M=M, Bv=5, seed=dh + M)
+    assert exact + loose == w.H
+
+
+def test_many_anchors(cast_lib):
+    """512 anchors of 13 chunks: the masks' LDS at its largest beside the staged u."""
+    anchors = tuple(range(1, 1025, 2))
+    w = _workload(1, 32, anchors)
+    (exact, loose), _ = run_case(cast_lib, w, anchors, 1026, 3, M=13, Bv=2)
+    assert exact + loose == w.H
