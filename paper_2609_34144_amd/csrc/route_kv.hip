@@ -19,34 +19,14 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// One block per (channel group of kMeansCh channels, segment); segment s < n_a is
-// anchor frame s of q (S tokens), the others are the history chunks of k, then (in
-// coupled routing) those of v (Bv tokens).  Wave w sums tokens [w T / 8, (w + 1) T / 8) of the segment: its lane
-// (row r = lane / 16, column = lane % 16) adds 8 consecutive bf16 channels of the
-// tokens t = r mod 4, so one load instruction reads 4 tokens x 256 contiguous
-// bytes, eight of them in flight.  The 4 rows are summed by two lane exchanges,
-// the 8 waves through LDS in wave order: a fixed order, so runs are bit-identical.
-__global__ __launch_bounds__(kMeansWaves * 64) void route_means_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    int n_a, int M, int S, int Bv, int D, float* __restrict__ means) {
-  __shared__ float red[kMeansWaves][kMeansCh];
-  const int grp = blockIdx.x, seg = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = lane & 15, row = lane >> 4;
-  const int c = grp * kMeansCh + col * 8;
-  const uint16_t* base;
-  int T;
-  if (seg < n_a) {
-    base = q + (long long)seg * S * D;
-    T = S;
-  } else {
-    const int m = seg - n_a;
-    base = m < M ? k + (long long)m * Bv * D : v + (long long)(m - M) * Bv * D;
-    T = Bv;
-  }
-  const int t0 = (int)((long long)T * wave / kMeansWaves);
-  const int t1 = (int)((long long)T * (wave + 1) / kMeansWaves);
-  float acc[8];
+// Lane (row r = lane / 16, column = lane % 16) of a wave adds 8 consecutive bf16
+// channels of the tokens t0 + r, t0 + r + 4, ... < t1 of a segment, so one load
+// instruction reads 4 tokens x 256 contiguous bytes, kFlight of them in flight; then
+// the 4 rows are summed by two lane exchanges (a fixed order, so runs are
+// bit-identical).  base points at the segment's channel c = the lane's first one.
+constexpr int kFlight = 8;   // loads in flight per lane
+__device__ __forceinline__ void sum_tokens(const uint16_t* __restrict__ base, int t0, int t1, int row,
+                                           int D, bool in, float (&acc)[8]) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
   auto add = [&](const u32x4& v) {
@@ -55,17 +35,17 @@ __global__ __launch_bounds__(kMeansWaves * 64) void route_means_kernel(
     acc[4] += bf16lo(v.z); acc[5] += bf16hi(v.z);
     acc[6] += bf16lo(v.w); acc[7] += bf16hi(v.w);
   };
-  if (c < D) {
+  if (in) {
     const long long step = (long long)D / 2;        // 4 tokens, in u32x4 units
-    const u32x4* p = reinterpret_cast<const u32x4*>(base + (long long)(t0 + row) * D + c);
+    const u32x4* p = reinterpret_cast<const u32x4*>(base + (long long)(t0 + row) * D);
     int t = t0 + row;
-    for (; t + 28 < t1; t += 32) {
-      u32x4 v[8];
+    for (; t + 4 * (kFlight - 1) < t1; t += 4 * kFlight) {
+      u32x4 v[kFlight];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = __builtin_nontemporal_load(p + u * step);
+      for (int u = 0; u < kFlight; ++u) v[u] = __builtin_nontemporal_load(p + u * step);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) add(v[u]);
-      p += 8 * step;
+      for (int u = 0; u < kFlight; ++u) add(v[u]);
+      p += kFlight * step;
     }
     for (; t < t1; t += 4) {
       add(__builtin_nontemporal_load(p));
@@ -77,19 +57,58 @@ __global__ __launch_bounds__(kMeansWaves * 64) void route_means_kernel(
     acc[e] += __shfl_xor(acc[e], 16);
     acc[e] += __shfl_xor(acc[e], 32);
   }
+}
+
+// The segments are the n_a anchor frames of q (S tokens each), then the M history
+// chunks of k and (in coupled routing) those of v (Bv tokens each).  A block of
+// kMeansWaves waves takes one group of kMeansCh channels of one anchor frame or of PACK
+// chunks; kMeansWaves / PACK waves share a segment, wave w of them summing tokens
+// [w T / n, (w + 1) T / n), and are added through LDS in wave order.
+// HBM-bound: 6.0 TB/s on 32 chunks of 3520 tokens (779 MB).  Short chunks leave
+// a wave one or two loads and the dispatcher one workgroup per 16 KB, so two chunks
+// share a workgroup (launch_pool_means has the line).
+template <int PACK>
+__global__ __launch_bounds__(kMeansWaves * 64) void route_means_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    int n_a, int M, int n_chunks, int S, int Bv, int D, float* __restrict__ means) {
+  constexpr int NWC = kMeansWaves / PACK;
+  __shared__ float red[kMeansWaves][kMeansCh];
+  const int grp = blockIdx.x, y = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = lane & 15, row = lane >> 4;
+  const int c = grp * kMeansCh + col * 8;
+  const bool anchor = y < n_a;
+  const int nw = anchor ? kMeansWaves : NWC;          // waves of this wave's segment
+  const int m = (y - n_a) * PACK + wave / NWC;        // its chunk, past the anchors
+  const int T = anchor ? S : Bv;
+  const uint16_t* base = anchor ? q + (long long)y * S * D
+                         : m < M ? k + (long long)m * Bv * D : v + (long long)(m - M) * Bv * D;
+  const int w = anchor ? wave : wave % NWC;
+  float acc[8];
+  sum_tokens(base + c, (int)((long long)T * w / nw), (int)((long long)T * (w + 1) / nw), row, D,
+                c < D && (anchor || m < n_chunks), acc);
   if (row == 0) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) red[wave][col * 8 + e] = acc[e];
   }
   __syncthreads();
-  if (threadIdx.x < kMeansCh) {
-    const int ch = grp * kMeansCh + threadIdx.x;
-    if (ch < D) {
-      float s = 0.0f;
+  const int ch = grp * kMeansCh + (threadIdx.x & (kMeansCh - 1));
+  const int part = threadIdx.x / kMeansCh;            // 4 x 128 threads
+  if (ch >= D) return;
+  if (anchor) {
+    if (part > 0) return;
+    float s = 0.0f;
 #pragma unroll
-      for (int w = 0; w < kMeansWaves; ++w) s += red[w][threadIdx.x];
-      means[(long long)seg * D + ch] = s / (float)T;
-    }
+    for (int x = 0; x < kMeansWaves; ++x) s += red[x][threadIdx.x];
+    means[(long long)y * D + ch] = s / (float)T;
+    return;
+  }
+  const int mo = (y - n_a) * PACK + part;
+  if (part < PACK && mo < n_chunks) {
+    float s = 0.0f;
+#pragma unroll
+    for (int x = 0; x < NWC; ++x) s += red[part * NWC + x][threadIdx.x & (kMeansCh - 1)];
+    means[(long long)(n_a + mo) * D + ch] = s / (float)T;
   }
 }
 
@@ -218,10 +237,19 @@ RoutePlan plan_route(int n_a, int S, int H, int dh, int M, int Bv) {
 
 cast_status_t launch_pool_means(const void* q, const void* k, const void* v, int n_a, int S, int M,
                                 int Bv, int D, float* means, hipStream_t stream) {
-  const int segs = n_a + M + (v != nullptr ? M : 0);
-  hipLaunchKernelGGL(route_means_kernel, dim3((D + kMeansCh - 1) / kMeansCh, segs), dim3(kMeansWaves * 64),
-                     0, stream, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
-                     static_cast<const uint16_t*>(v), n_a, M, S, Bv, D, means);
+  const int n_chunks = v != nullptr ? 2 * M : M;
+  const int groups = (D + kMeansCh - 1) / kMeansCh;
+  // Two chunks per workgroup where that was faster: chunks of 64 tokens on grids that
+  // one workgroup per chunk makes long (1764 segments x 24 groups: 156.7 -> 149.9 us a
+  // call; 393 x 12 groups 27.9 against 28.1) and shorter chunks on any grid (256 of 16
+  // tokens: 19.8 -> 15.5 us).  At 128 tokens it lost (512 x 24 groups: 71.4 -> 76.3).
+  constexpr int P = 2;
+  const bool pack = Bv <= 32 || (Bv <= 64 && (long long)n_chunks * groups >= 16384);
+  const int rows = n_a + (pack ? (n_chunks + P - 1) / P : n_chunks);
+  hipLaunchKernelGGL((pack ? route_means_kernel<P> : route_means_kernel<1>), dim3(groups, rows),
+                     dim3(kMeansWaves * 64), 0, stream, static_cast<const uint16_t*>(q),
+                     static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), n_a, M, n_chunks,
+                     S, Bv, D, means);
   return check_launch("route_means");
 }
 

@@ -134,10 +134,10 @@ __device__ __forceinline__ void topk_words(const uint32_t (&key)[KPT], const boo
   }
 }
 
-// Writes the indices of the set winner bits in ascending order to dst.
+// Writes the indices of the set winner bits in ascending order to dst, the first `most`.
 template <int NW, int KPT>
 __device__ __forceinline__ void write_indices(const unsigned long long (&win)[KPT], Scratch& s, int& par,
-                                              int32_t* __restrict__ dst) {
+                                              int32_t* __restrict__ dst, int most = 1 << 30) {
   int mine = 0;
 #pragma unroll
   for (int j = 0; j < KPT; ++j) mine += __popcll(win[j]);
@@ -147,8 +147,8 @@ __device__ __forceinline__ void write_indices(const unsigned long long (&win)[KP
   const int wave = NW == 1 ? 0 : (int)(threadIdx.x >> 6);
 #pragma unroll
   for (int j = 0; j < KPT; ++j) {
-    if ((win[j] >> lane) & 1ull)
-      dst[pos + __popcll(win[j] & ((1ull << lane) - 1ull))] = (wave * KPT + j) * 64 + lane;
+    const int at = pos + __popcll(win[j] & ((1ull << lane) - 1ull));
+    if (((win[j] >> lane) & 1ull) && at < most) dst[at] = (wave * KPT + j) * 64 + lane;
     pos += __popcll(win[j]);
   }
 }
