@@ -7,15 +7,16 @@
 //               allow them) and writes one partial, so the sums are bit-identical
 //               across runs.
 // frame_select  one block: per present branch r_i = sqrt(sum / (S D)) (partials
-//               added in fp64 by one wave per frame, fixed order), min / max over
+//               added in fp64 by half a wave per frame, fixed order), min / max over
 //               the chunk, the normalised responses and their mean d_i; ages after
 //               the block's anchors, coverage debt h_i / ceil(N / K_f), score
 //               d_i + lambda D_i (lambda D_i without a fresh response); the K_f
-//               best frames by rank counting under (score descending, frame
+//               best frames by counting (topk_select.h) under (score descending, frame
 //               ascending), written in ascending frame order.  Every float operation after r is one
 //               correctly rounded fp32 operation (no contraction), so the
 //               decision is reproducible on the host in fp32.
 #include "cast_common.h"
+#include "topk_select.h"
 
 namespace cast {
 
@@ -119,92 +120,140 @@ struct SelArgs {
   uint32_t prev_mask[kSelectMaxFrames / 32];   // anchors the block ran with
 };
 
+// Normalised responses, ages, debt and score of frame i, each float operation rounded
+// once, in the documented order.  Stores the frame's age and score.
+__device__ __forceinline__ float frame_score(const SelArgs& a, int i, int age, const float (&ri)[2],
+                                             const float (&lo)[2], const float (&hi)[2]) {
+  const int h_cov = (a.n_cur + a.k_f - 1) / a.k_f;
+  float d = 0.0f;
+#pragma unroll
+  for (int z = 0; z < 2; ++z)
+    if (z < a.n_present)
+      d = __fadd_rn(d, __fdiv_rn(__fsub_rn(ri[z], lo[z]), __fadd_rn(__fsub_rn(hi[z], lo[z]), a.eps)));
+  if (a.n_present == 2) d = __fmul_rn(d, 0.5f);
+  const bool was_anchor = (a.prev_mask[i >> 5] >> (i & 31)) & 1u;
+  const int h = was_anchor ? 0 : age + 1;
+  a.ages[i] = h;
+  const float debt = __fdiv_rn((float)h, (float)h_cov);
+  const float ld = __fmul_rn(a.lambda_cov, debt);
+  const float s = a.n_present > 0 ? __fadd_rn(d, ld) : ld;
+  if (a.score_out) a.score_out[i] = s;
+  return s;
+}
+
+// The K_f best of the scores held at (wave, slot, lane), written in ascending frame
+// order.  A NaN score beats nothing and is beaten by nothing: it is always chosen, and
+// the first K_f chosen frames are written.
+template <int NW, int KPT>
+__device__ __forceinline__ void choose_frames(const SelArgs& a, const float (&sc)[KPT], const bool (&in)[KPT],
+                                              sel::Scratch& scratch) {
+  uint32_t key[KPT];
+  bool valid[KPT];
+  unsigned long long win[KPT], nan[KPT];
+  int mine = 0, before, n_ok, par = 0;
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    nan[j] = __ballot(in[j] && sc[j] != sc[j]);
+    valid[j] = in[j] && sc[j] == sc[j];
+    key[j] = valid[j] ? sel::order_key(sc[j]) : 0u;
+    win[j] = 0ull;
+    mine += __popcll(__ballot(valid[j]));
+  }
+  sel::wave_prefix<NW>(mine, scratch, par, before, n_ok);
+  if (n_ok > 0) sel::topk_words<NW, KPT>(key, valid, min(a.k_f, n_ok), scratch, par, win);
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) win[j] |= nan[j];
+  sel::write_indices<NW, KPT>(win, scratch, par, a.anchors_out, a.k_f);
+}
+
+// Bound by latency: the partials' loads, then a chain of small reductions.  Up to 64
+// frames (every chunk in use) the first wave finishes alone, one frame per lane, with
+// no barrier after the sums; more frames take all 16 waves.  16 frames of
+// 44x80x3072 in two branches: 9.6 -> 7.5 us (half of it the 330 partials per frame); a
+// call of 8 frames of 30x52x1536 19.1 -> 18.2, of 300 frames 48 -> 31, of 4096 1193 ->
+// 210 us (the ranks were counted over all frames, the positions from one by one).
 __global__ __launch_bounds__(kSelThreads) void frame_select_kernel(SelArgs a) {
   __shared__ float r[2][kSelectMaxFrames];
-  __shared__ float sc[kSelectMaxFrames];
-  __shared__ unsigned char sel[kSelectMaxFrames];
   __shared__ float red[2][kSelThreads / 64];
-  __shared__ float lohi[2][2];
+  __shared__ sel::Scratch scratch;
   const int tid = threadIdx.x, n = a.n_cur;
-
-  // r per present branch: one wave per (branch, frame) adds its partials in fp64,
-  // lane l taking partials l, l + 64, ..., then a fixed butterfly
   const int wave = tid >> 6, lane = tid & 63;
-  for (int item = wave; item < a.n_present * n; item += kSelThreads / 64) {
+  // r per present branch: half a wave per (branch, frame) adds its partials in fp64,
+  // lane l taking partials l, l + 32, ..., then a fixed butterfly
+  const int half = tid >> 5, l32 = tid & 31;
+  for (int item = half; item < a.n_present * n; item += kSelThreads / 32) {
     const int z = item / n, i = item - z * n;
     const float* p = a.partial + (long long)item * a.n_split;
     double sum = 0.0;
-    for (int k = lane; k < a.n_split; k += 64) sum += (double)p[k];
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if (lane == 0) {
+#pragma unroll 12
+    for (int k = l32; k < a.n_split; k += 32) sum += (double)p[k];
+    for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if (l32 == 0) {
       const float ri = (float)sqrt(sum * a.inv_elems);
       r[z][i] = ri;
       if (a.r_out) a.r_out[(long long)a.row_of[z] * n + i] = ri;
     }
   }
-  __syncthreads();
+  if (n <= 64) {
+    const int age = wave == 0 && lane < n ? a.ages[lane] : 0;
+    __syncthreads();
+    if (wave != 0) return;
+    float ri[2], lo[2], hi[2];
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+      const bool in = z < a.n_present && lane < n;
+      ri[z] = in ? r[z][lane] : 0.0f;
+      lo[z] = in ? ri[z] : INFINITY;
+      hi[z] = in ? ri[z] : -INFINITY;
+      if (z < a.n_present)
+        for (int o = 32; o > 0; o >>= 1) {
+          lo[z] = fminf(lo[z], __shfl_xor(lo[z], o));
+          hi[z] = fmaxf(hi[z], __shfl_xor(hi[z], o));
+        }
+    }
+    float sc[1] = {0.0f};
+    bool in[1] = {lane < n};
+    if (in[0]) sc[0] = frame_score(a, lane, age, ri, lo, hi);
+    choose_frames<1, 1>(a, sc, in, scratch);
+    return;
+  }
+  sel::clear_scratch(scratch);
   // min and max over the chunk, per branch (exact in any order)
+  float lo[2], hi[2];
   for (int z = 0; z < a.n_present; ++z) {
-    float lo = INFINITY, hi = -INFINITY;
+    float mn = INFINITY, mx = -INFINITY;
     for (int i = tid; i < n; i += kSelThreads) {
-      lo = fminf(lo, r[z][i]);
-      hi = fmaxf(hi, r[z][i]);
+      mn = fminf(mn, r[z][i]);
+      mx = fmaxf(mx, r[z][i]);
     }
     for (int o = 32; o > 0; o >>= 1) {
-      lo = fminf(lo, __shfl_xor(lo, o));
-      hi = fmaxf(hi, __shfl_xor(hi, o));
+      mn = fminf(mn, __shfl_xor(mn, o));
+      mx = fmaxf(mx, __shfl_xor(mx, o));
     }
-    if ((tid & 63) == 0) { red[0][tid >> 6] = lo; red[1][tid >> 6] = hi; }
+    if (lane == 0) { red[0][wave] = mn; red[1][wave] = mx; }
     __syncthreads();
-    if (tid == 0) {
-      lo = red[0][0];
-      hi = red[1][0];
-      for (int w = 1; w < kSelThreads / 64; ++w) {
-        lo = fminf(lo, red[0][w]);
-        hi = fmaxf(hi, red[1][w]);
-      }
-      lohi[z][0] = lo;
-      lohi[z][1] = hi;
+    lo[z] = red[0][0];
+    hi[z] = red[1][0];
+    for (int w = 1; w < kSelThreads / 64; ++w) {
+      lo[z] = fminf(lo[z], red[0][w]);
+      hi[z] = fmaxf(hi[z], red[1][w]);
     }
     __syncthreads();
   }
-  // sensitivity, ages, debt and score per frame
-  const int h_cov = (n + a.k_f - 1) / a.k_f;
-  for (int i = tid; i < n; i += kSelThreads) {
-    float d = 0.0f;
-    for (int z = 0; z < a.n_present; ++z) {
-      const float lo = lohi[z][0], hi = lohi[z][1];
-      const float nz = __fdiv_rn(__fsub_rn(r[z][i], lo), __fadd_rn(__fsub_rn(hi, lo), a.eps));
-      d = __fadd_rn(d, nz);
+  constexpr int KPT = kSelectMaxFrames / kSelThreads;
+  float sc[KPT];
+  bool in[KPT];
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    const int i = (wave * KPT + j) * 64 + lane;
+    in[j] = i < n;
+    sc[j] = 0.0f;
+    if (in[j]) {
+      const float ri[2] = {a.n_present > 0 ? r[0][i] : 0.0f, a.n_present > 1 ? r[1][i] : 0.0f};
+      sc[j] = frame_score(a, i, a.ages[i], ri, lo, hi);
     }
-    if (a.n_present == 2) d = __fmul_rn(d, 0.5f);
-    const bool was_anchor = (a.prev_mask[i >> 5] >> (i & 31)) & 1u;
-    const int h = was_anchor ? 0 : a.ages[i] + 1;
-    a.ages[i] = h;
-    const float debt = __fdiv_rn((float)h, (float)h_cov);
-    const float ld = __fmul_rn(a.lambda_cov, debt);
-    const float s = a.n_present > 0 ? __fadd_rn(d, ld) : ld;
-    sc[i] = s;
-    if (a.score_out) a.score_out[i] = s;
   }
-  __syncthreads();
-  // TopK under (score descending, frame ascending) by rank counting
-  for (int i = tid; i < n; i += kSelThreads) {
-    const float si = sc[i];
-    int rank = 0;
-    for (int j = 0; j < n; ++j) {
-      const float sj = sc[j];
-      rank += (sj > si) || (sj == si && j < i);
-    }
-    sel[i] = rank < a.k_f;
-  }
-  __syncthreads();
-  for (int i = tid; i < n; i += kSelThreads) {
-    if (!sel[i]) continue;
-    int pos = 0;
-    for (int j = 0; j < i; ++j) pos += sel[j];
-    if (pos < a.k_f) a.anchors_out[pos] = i;   // (NaN scores could select more)
-  }
+  choose_frames<kSelThreads / 64, KPT>(a, sc, in, scratch);
 }
 
 }  // namespace
