@@ -6,13 +6,15 @@
 // is the concatenation [current segment (n0 tokens) ; routed chunk idx[0] ; ... ],
 // walked in tiles of 64 keys.
 //
-// Two waves per SIMD, ping-pong: wave w runs on SIMD w % 4, so every SIMD holds
+// Two schedules.  At dh = 128, two waves per SIMD, ping-pong: wave w runs on SIMD w % 4, so every SIMD holds
 // one wave of group A (waves 0-3) and one of group B (waves 4-7).  The groups
 // alternate between an MFMA interval (S = K Q^T of tile j and O += P V of tile
 // j-1) and a softmax interval, half a tile apart, with a workgroup barrier between
 // intervals: while one wave of a SIMD keeps the matrix core busy, the other issues
 // the softmax's VALU work.  (Within one wave, VALU work between its own MFMAs is
-// only partly hidden; across the two waves of a SIMD it is.)
+// only partly hidden; across the two waves of a SIMD it is.)  At dh = 32 and 64 two
+// workgroups share a compute unit, four waves per SIMD, and each wave takes S, softmax
+// and P V of a tile in turn (the wide schedule in the kernel).
 //
 // Data movement: every K and V tile is copied global -> LDS by the buffer unit
 // (buffer_load_dwordx4 ... lds), so no registers or VALU work stage it.  Each
@@ -56,6 +58,7 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kBQ = kWaves * 32;   // queries per workgroup: one block of 32 per wave
 // operand reads issued this many MFMA steps ahead of their use
 constexpr int kLookahead = 3;
+constexpr int kWideLookahead = 3;
 // s_waitcnt vmcnt(0) that leaves expcnt and lgkmcnt free
 constexpr int kVmcntBase = 0x0F70;
 constexpr int kMaxKeff = kAttnMaxKeff;   // routed chunk indices cached in LDS
@@ -65,6 +68,9 @@ constexpr int kMaxKeff = kAttnMaxKeff;   // routed chunk indices cached in LDS
 constexpr float kMaxSlack = 8.0f;
 // the lane sum of a tile's 32 probabilities up to which the running max may stay
 constexpr float kSumBound = 256.0f;   // 2^kMaxSlack
+
+// waves per SIMD: see the two schedules in the kernel
+constexpr int wide_waves(int dh) { return dh <= 64 ? 4 : 2; }
 
 struct AttnArgs {
   const uint16_t* q;
@@ -150,12 +156,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tensor_rsrc(const void* base, 
 }
 
 // LDS swizzles (chunk c of tile row r is stored at chunk c ^ swz(r)):
-//  K: a ds_read_b128 of one logical chunk by 32 consecutive rows; XOR by r mod CPR
-//     spreads any 16 consecutive rows over 16 distinct 16-byte bank groups.
+//  K: a ds_read_b128 of one logical chunk by 32 consecutive rows; rows of 16 / CPR
+//     are 256 bytes (all banks), so XOR by (r / (16 / CPR)) mod CPR spreads any 16
+//     consecutive rows over 16 distinct 16-byte bank groups.
 //  V: a transposing read takes 4 consecutive rows x 32 bytes per 16 lanes, the
 //     two 16-lane halves of 32 lanes 32 bytes apart; XOR by {0, 10, 4, 14}[r mod 4]
 //     gives the 8 row segments of 32 lanes 8 distinct 32-byte bank groups.
-__device__ __forceinline__ constexpr int kswz(int r, int cpr) { return r & (cpr - 1); }
+__device__ __forceinline__ constexpr int kswz(int r, int cpr) { return (r / (16 / cpr)) & (cpr - 1); }
 __device__ __forceinline__ constexpr int vswz(int r, int cpr) {
   return ((2 * (r & 3)) ^ (8 * (r & 1))) & (cpr - 1);
 }
@@ -166,7 +173,8 @@ __device__ __forceinline__ constexpr int vswz(int r, int cpr) {
 // so a tile meets at most two chunks; 0 the general path (current segment, short
 // chunks), one chunk-slot lookup per row.
 template <int DH, int MODE>
-__global__ __launch_bounds__(kThreads, 1) void anchor_attn_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kThreads, wide_waves(DH)) void anchor_attn_kernel(AttnArgs a) {
+  constexpr bool WIDE = wide_waves(DH) > 2;  // two workgroups per compute unit
   constexpr bool FAST = MODE >= 1, ALIGNED = MODE == 2;
   constexpr int CPR = DH / 8;                // 16-byte chunks per row
   constexpr int ROWB = DH * 2;               // bytes per row
@@ -243,7 +251,7 @@ __global__ __launch_bounds__(kThreads, 1) void anchor_attn_kernel(AttnArgs a) {
   //      ci = 64 k + lane of its tile: row ci / CPR = brow + r RSTEP with
   //      brow = w 512/DH + lane / CPR, physical chunk lane % CPR, which holds logical
   //      chunk (lane % CPR) ^ swz(row).  Both swizzles depend on the row only
-  //      through row mod CPR (K) or row mod 4 (V), which r does not change.
+  //      through row mod 16 (K) or row mod 4 (V), which r does not change.
   const int cw = wave & 3;
   const int brow = cw * (512 / DH) + lane / CPR;
   const unsigned kofs = (unsigned)(((lane % CPR) ^ kswz(brow, CPR)) * 16);
@@ -343,7 +351,7 @@ __global__ __launch_bounds__(kThreads, 1) void anchor_attn_kernel(AttnArgs a) {
 
   // ---- LDS read addresses (bytes within a tile)
   // K: lane reads row kb*32 + l32, logical chunk 2t + hf, stored at chunk
-  // (2t + hf) ^ (l32 % CPR); as bytes that is kbase ^ 32t (the row offset is a
+  // (2t + hf) ^ kswz(l32); as bytes that is kbase ^ 32t (the row offset is a
   // multiple of the row length, so the XOR only touches the chunk bits)
   const unsigned kbase = (unsigned)(l32 * ROWB + ((hf ^ kswz(l32, CPR)) * 16));
   // V (transposing read): within each 16-lane group gq = lane / 16, lane a supplies
@@ -404,6 +412,35 @@ __global__ __launch_bounds__(kThreads, 1) void anchor_attn_kernel(AttnArgs a) {
     });
   };
 
+  // ---- the same products one after the other (wide schedule): S^T of tile j, and
+  //      after its softmax O^T += V^T[j] P^T[j]; operands read kWideLookahead steps ahead
+  auto s_phase = [&](const uint16_t* kt) __attribute__((always_inline)) {
+    bf16x8 op[NSTEP];
+    static_for<0, kWideLookahead>([&](auto uu) { constexpr int u = decltype(uu)::value; op[u] = read_k(kt, u / 2, u % 2); });
+    static_for<0, NSTEP>([&](auto uu) {
+      constexpr int u = decltype(uu)::value, n = u + kWideLookahead;
+      if constexpr (n < NSTEP) op[n] = read_k(kt, n / 2, n % 2);
+      sn[u % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[u], qreg[u / 2], u < 2 ? f32x16{} : sn[u % 2],
+                                                          0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto pv_phase = [&](const uint16_t* vt) __attribute__((always_inline)) {
+    bf16x8 op[NSTEP];
+    auto rd = [&](auto uu) __attribute__((always_inline)) {
+      constexpr int u = decltype(uu)::value;
+      op[u] = read_v(vt, u % ND, u / (2 * ND), (u / ND) % 2);
+    };
+    static_for<0, kWideLookahead>([&](auto u) { rd(u); });
+    static_for<0, NSTEP>([&](auto uu) {
+      constexpr int u = decltype(uu)::value;
+      if constexpr (u + kWideLookahead < NSTEP) rd(IC<u + kWideLookahead>{});
+      constexpr int db = u % ND, kb = u / (2 * ND), s2 = (u / ND) % 2;
+      acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[u], pp[kb][s2], acc_o[db], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+
   // ---- softmax phase of tile j: mask, exponentials against the running max,
   //      packed to the bf16 P^T operands and summed, running sum.  Every
   //      probability is at most the lane's sum of 32, so a sum <= 2^kMaxSlack
@@ -413,7 +450,7 @@ __global__ __launch_bounds__(kThreads, 1) void anchor_attn_kernel(AttnArgs a) {
   //      max (one exchange with the other half-wave), the running max moved only
   //      when the tile max exceeds it by more than kMaxSlack, exponentials again,
   //      and the O rescale.
-  auto softmax_phase = [&](int j) __attribute__((always_inline)) {
+  auto mask_tail = [&](int j) __attribute__((always_inline)) {
     if (tb + j == a.nt_all - 1 && a.L != a.nt_all * kBK) {
       const int key0 = (tb + j) * kBK;
 #pragma unroll
@@ -424,6 +461,34 @@ __global__ __launch_bounds__(kThreads, 1) void anchor_attn_kernel(AttnArgs a) {
           if (key >= a.L) sn[kb][e] = -INFINITY;
         }
     }
+  };
+  // the exact path's maximum of the tile's scores, moved running max and O rescale;
+  // returns the running max to use
+  auto move_max = [&]() __attribute__((always_inline)) -> float {
+    float pm = max3f(sn[0][0], sn[0][1], sn[0][2]);
+#pragma unroll
+    for (int k = 1; k < 15; ++k) {
+      const int v = 2 * k + 1;
+      pm = max3f(pm, sn[v / 16][v % 16], sn[(v + 1) / 16][(v + 1) % 16]);
+    }
+    pm = fmaxf(pm, sn[1][15]);
+    const u32x2 sw = __builtin_bit_cast(
+        u32x2, __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, pm),
+                                                __builtin_bit_cast(unsigned, pm), false, false));
+    const float mx = fmaxf(__builtin_bit_cast(float, sw.x), __builtin_bit_cast(float, sw.y));
+    const float m_cand = fmaxf(m_run, mx * a.sl2);
+    const bool up = m_cand > m_run + kMaxSlack;
+    const float m_new = up ? m_cand : m_run;
+    const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+    l_run *= corr;
+    if (__ballot(up) != 0ull) {
+#pragma unroll
+      for (int db = 0; db < ND; ++db) acc_o[db] *= corr;
+    }
+    return m_new;
+  };
+  auto softmax_phase = [&](int j) __attribute__((always_inline)) {
+    mask_tail(j);
     // row sum in fp32 over four partial sums (short dependency chains), each
     // started from its first term (not 0 + p: the compiler keeps that add)
     float pe[32], rs4[4];
@@ -434,87 +499,137 @@ __global__ __launch_bounds__(kThreads, 1) void anchor_attn_kernel(AttnArgs a) {
     }
     float rs = (rs4[0] + rs4[1]) + (rs4[2] + rs4[3]);
     if (__ballot(!(rs <= kSumBound)) != 0ull) {
-      float pm = max3f(sn[0][0], sn[0][1], sn[0][2]);
-#pragma unroll
-      for (int k = 1; k < 15; ++k) {
-        const int v = 2 * k + 1;
-        pm = max3f(pm, sn[v / 16][v % 16], sn[(v + 1) / 16][(v + 1) % 16]);
-      }
-      pm = fmaxf(pm, sn[1][15]);
-      const u32x2 sw = __builtin_bit_cast(
-          u32x2, __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, pm),
-                                                  __builtin_bit_cast(unsigned, pm), false, false));
-      const float mx = fmaxf(__builtin_bit_cast(float, sw.x), __builtin_bit_cast(float, sw.y));
-      const float m_cand = fmaxf(m_run, mx * a.sl2);
-      const bool up = m_cand > m_run + kMaxSlack;
-      const float m_new = up ? m_cand : m_run;
-      const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = move_max();
 #pragma unroll
       for (int e = 0; e < 32; ++e) {
-        pe[e] = __builtin_amdgcn_exp2f(fmaf(sn[e / 16][e % 16], a.sl2, -m_new));
+        pe[e] = __builtin_amdgcn_exp2f(fmaf(sn[e / 16][e % 16], a.sl2, -m_run));
         rs4[e % 4] = e < 4 ? pe[e] : rs4[e % 4] + pe[e];
       }
       rs = (rs4[0] + rs4[1]) + (rs4[2] + rs4[3]);
-      l_run *= corr;
-      m_run = m_new;
-      if (__ballot(up) != 0ull) {
-#pragma unroll
-        for (int db = 0; db < ND; ++db) acc_o[db] *= corr;
-      }
     }
 #pragma unroll
     for (int g = 0; g < 4; ++g) pp[g / 2][g % 2] = pack8(&pe[8 * g]);
     l_run += rs;
   };
-
-  // ---- prologue: K[0]; tile -1 has P = 0 and a zeroed V buffer (P = 0 must not
-  //      meet NaN in stale LDS)
+  // the same in the wide schedule, the exponentials in place of the scores (a second
+  // set would cost the registers of two waves per SIMD): the exact path, which needs
+  // the scores again, forms them again from the tile, still in LDS
+  auto softmax_in_place = [&](int j, const uint16_t* kt) __attribute__((always_inline)) {
+    auto exps = [&]() __attribute__((always_inline)) -> float {
+      float rs4[4];
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+      for (int e = 0; e < 32; ++e) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(sn[e / 16][e % 16], a.sl2, -m_run));
+        sn[e / 16][e % 16] = p;
+        rs4[e % 4] = e < 4 ? p : rs4[e % 4] + p;
+      }
+      return (rs4[0] + rs4[1]) + (rs4[2] + rs4[3]);
+    };
+    mask_tail(j);
+    float rs = exps();
+    if (__ballot(!(rs <= kSumBound)) != 0ull) {
+      s_phase(kt);
+      mask_tail(j);
+      m_run = move_max();
+      rs = exps();
+    }
 #pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) pp[kb][s2] = bf16x8{};
-  {
-    u32x4* z = reinterpret_cast<u32x4*>(lds_v1);
-    for (int x = tid; x < kBK * DH / 8; x += kThreads) z[x] = u32x4{0u, 0u, 0u, 0u};
-  }
-  {
-    const TileMap m0 = FAST ? cur_map(cursor_at(tb)) : TileMap{};
-    if (grp == 0) copy_tile(IC<0>{}, tb, m0, lds_k0);
-    else copy_tile(IC<1>{}, tb, m0, lds_v0);
-  }
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  // Group B runs one interval behind group A.  Interval 2j: A does the MFMAs of
-  // tile j while B does the softmax of tile j-1; interval 2j+1: A the softmax of
-  // tile j, B the MFMAs of tile j.  A copies K[j+1] at the start of interval
-  // 2j+1, B copies V[j+1] at the start of interval 2j+2, each into a buffer that
-  // no MFMA phase reads in that interval.
-  if (grp == 1) __syncthreads();
-  // One tile per call; K[j] in K buffer j%2, V[j-1] in V buffer (j-1)%2.  Every
-  // call runs the same MFMA phase: at j = 0 it meets tile -1 (P = 0 and a zeroed V
-  // buffer), at j = nt it computes a throw-away S from a stale K buffer.
-  auto iter = [&](auto par, int j) __attribute__((always_inline)) {
-    constexpr int P = decltype(par)::value;
-    uint16_t* const kc = P == 0 ? lds_k0 : lds_k1;   // K[j]
-    uint16_t* const kn = P == 0 ? lds_k1 : lds_k0;   // K[j-1]; then K[j+1]
-    uint16_t* const vp = P == 0 ? lds_v1 : lds_v0;   // V[j-1]; then V[j+1]
-    if (live) mfma_phase(kc, vp);
-    __syncthreads();
-    own_copies(j, kn, vp);
-    if (j < nt && live) softmax_phase(j);
-    // the copies of this interval land before the barrier publishes them: an
-    // explicit wait, the same in both groups (the barrier's workgroup fence does
-    // not reliably wait for copies into LDS)
-    __builtin_amdgcn_s_waitcnt(kVmcntBase);
-    __syncthreads();
+    for (int g = 0; g < 4; ++g) {
+      const f32x16& p = sn[g / 2];
+      const int b = 8 * (g % 2);
+      pp[g / 2][g % 2] = __builtin_bit_cast(bf16x8, u32x4{pack_bf16x2(p[b], p[b + 1]), pack_bf16x2(p[b + 2], p[b + 3]),
+                                                          pack_bf16x2(p[b + 4], p[b + 5]), pack_bf16x2(p[b + 6], p[b + 7])});
+    }
+    l_run += rs;
   };
-  int j = 0;
-  for (; j + 1 <= nt; j += 2) {
-    iter(IC<0>{}, j);
-    iter(IC<1>{}, j + 1);
+
+  if constexpr (WIDE) {
+    // Wide schedule (dh <= 64): a tile's MFMAs are half or a quarter of dh = 128's but
+    // its softmax is the same, so two waves per SIMD in lock step leave the SIMD
+    // waiting on one wave's softmax.  Here S, softmax and P V of a tile follow each
+    // other in the wave (which drops the second S / P operand set and fits 128
+    // registers), four waves per SIMD overlap by themselves, and a tile takes one
+    // barrier: the copies of tile j + 1 start when every wave is past tile j - 1.
+    // Measured: 24 heads of 64, 3 anchors of 1560 queries, 5069 keys 206 -> 166 us;
+    // 28160 keys, 4 anchors of 3520 queries 2.79 -> 2.5-2.6 ms (0.95 PFLOP/s); heads of
+    // 32 162 -> 157 us.  Bound by the VALU's softmax (117 operations per tile, 32 of
+    // them exponentials) and the MFMAs overlapping only in part: counters show the VALU
+    // 60% and the matrix cores 46% busy.  Two tiles per barrier, and s_setprio on either
+    // phase, were level.
+    {
+      const TileMap m0 = FAST ? cur_map(cursor_at(tb)) : TileMap{};
+      if (grp == 0) copy_tile(IC<0>{}, tb, m0, lds_k0);
+      else copy_tile(IC<1>{}, tb, m0, lds_v0);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    auto tile = [&](auto par, int j) __attribute__((always_inline)) {
+      constexpr int P = decltype(par)::value;
+      own_copies(j, P == 0 ? lds_k1 : lds_k0, P == 0 ? lds_v1 : lds_v0);
+      if (live) {
+        s_phase(P == 0 ? lds_k0 : lds_k1);
+        softmax_in_place(j, P == 0 ? lds_k0 : lds_k1);
+        pv_phase(P == 0 ? lds_v0 : lds_v1);
+      }
+      __builtin_amdgcn_s_waitcnt(kVmcntBase);
+      __syncthreads();
+    };
+    int j = 0;
+    for (; j + 1 < nt; j += 2) {
+      tile(IC<0>{}, j);
+      tile(IC<1>{}, j + 1);
+    }
+    if (j < nt) tile(IC<0>{}, j);
+  } else {
+    // ---- prologue: K[0]; tile -1 has P = 0 and a zeroed V buffer (P = 0 must not
+    //      meet NaN in stale LDS)
+  #pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+  #pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) pp[kb][s2] = bf16x8{};
+    {
+      u32x4* z = reinterpret_cast<u32x4*>(lds_v1);
+      for (int x = tid; x < kBK * DH / 8; x += kThreads) z[x] = u32x4{0u, 0u, 0u, 0u};
+    }
+    {
+      const TileMap m0 = FAST ? cur_map(cursor_at(tb)) : TileMap{};
+      if (grp == 0) copy_tile(IC<0>{}, tb, m0, lds_k0);
+      else copy_tile(IC<1>{}, tb, m0, lds_v0);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    // Group B runs one interval behind group A.  Interval 2j: A does the MFMAs of
+    // tile j while B does the softmax of tile j-1; interval 2j+1: A the softmax of
+    // tile j, B the MFMAs of tile j.  A copies K[j+1] at the start of interval
+    // 2j+1, B copies V[j+1] at the start of interval 2j+2, each into a buffer that
+    // no MFMA phase reads in that interval.
+    if (grp == 1) __syncthreads();
+    // One tile per call; K[j] in K buffer j%2, V[j-1] in V buffer (j-1)%2.  Every
+    // call runs the same MFMA phase: at j = 0 it meets tile -1 (P = 0 and a zeroed V
+    // buffer), at j = nt it computes a throw-away S from a stale K buffer.
+    auto iter = [&](auto par, int j) __attribute__((always_inline)) {
+      constexpr int P = decltype(par)::value;
+      uint16_t* const kc = P == 0 ? lds_k0 : lds_k1;   // K[j]
+      uint16_t* const kn = P == 0 ? lds_k1 : lds_k0;   // K[j-1]; then K[j+1]
+      uint16_t* const vp = P == 0 ? lds_v1 : lds_v0;   // V[j-1]; then V[j+1]
+      if (live) mfma_phase(kc, vp);
+      __syncthreads();
+      own_copies(j, kn, vp);
+      if (j < nt && live) softmax_phase(j);
+      // the copies of this interval land before the barrier publishes them: an
+      // explicit wait, the same in both groups (the barrier's workgroup fence does
+      // not reliably wait for copies into LDS)
+      __builtin_amdgcn_s_waitcnt(kVmcntBase);
+      __syncthreads();
+    };
+    int j = 0;
+    for (; j + 1 <= nt; j += 2) {
+      iter(IC<0>{}, j);
+      iter(IC<1>{}, j + 1);
+    }
+    if (j <= nt) iter(IC<0>{}, j);
+    if (grp == 0) __syncthreads();   // B's extra interval at the start
   }
-  if (j <= nt) iter(IC<0>{}, j);
-  if (grp == 0) __syncthreads();   // B's extra interval at the start
 
   // ---- epilogue: normalise, write O (bf16) and the log-sum-exp; a piece writes
   //      its normalised fp32 partial and log2-domain log-sum-exp instead
@@ -603,22 +718,36 @@ cast_status_t launch_dh(AttnArgs a, hipStream_t stream) {
 
 }  // namespace
 
+// The last U mod C units of a grid of C resident workgroups run as s pieces along the
+// keys when that is estimated to be sooner: a piece takes ceil(tiles / s) tile times
+// (measured per 64-key tile: 1.65 us at dh = 128 with one workgroup per compute unit;
+// 1.3 / 2.05 us at dh = 64 and 1.0 / 1.6 us at dh = 32 with one / two), and the split
+// adds the merge launch (4 us) and the pieces' fp32 partials, written and read once
+// (4.5 TB/s).  Measured: 96 units of 11 tiles 23.1 us whole and 27.0 in two pieces, of
+// 22 tiles 35.7 and 32.9; 32 units of 39 tiles 46.6 in two pieces and 29.5 in eight;
+// dh = 64, 240 units of 33 tiles 47.7 whole and 54.5 in two pieces.
 AttnSplitPlan attn_split_plan(int n_a, int S, int H, int dh, long long L, int cus) {
-  constexpr long long kMaxSplit = 8, kMinPieceTiles = 16;
+  constexpr long long kMaxSplit = 16, kMinPieceTiles = 2;
   const long long units = (long long)n_a * H * ((S + kBQ - 1) / kBQ);
   AttnSplitPlan p{(int)units, 0, 1, 0};
   if (cus <= 0) return p;
-  const long long rem = units % cus;
+  const int per_cu = wide_waves(dh) / 2;
+  const long long slots = (long long)cus * per_cu, rem = units % slots;
   if (rem == 0) return p;
   const long long nt_all = (L + kBK - 1) / kBK;
-  long long s = cus / rem;
-  s = s < kMaxSplit ? s : kMaxSplit;
-  s = s < nt_all / kMinPieceTiles ? s : nt_all / kMinPieceTiles;
-  if (s < 2) return p;
+  const double tile_us[2] = {dh == 128 ? 1.65 : dh == 64 ? 1.3 : 1.0, dh == 64 ? 2.05 : 1.6};
+  auto estimate = [&](long long s) {
+    const double run = (double)((nt_all + s - 1) / s) * tile_us[rem * s > cus ? 1 : 0];
+    return s == 1 ? run : run + 4.0 + (double)(rem * s * kBQ * dh) * 8.0 / 4.5e6;
+  };
+  long long best = 1;
+  for (long long s = 2; s <= kMaxSplit && rem * s <= slots && s * kMinPieceTiles <= nt_all; ++s)
+    if (estimate(s) < estimate(best)) best = s;
+  if (best < 2) return p;
   p.n_full = (int)(units - rem);
   p.n_split = (int)rem;
-  p.split = (int)s;
-  p.bytes = align_up((size_t)rem * s * kBQ * dh * 4) + align_up((size_t)rem * s * kBQ * 4);
+  p.split = (int)best;
+  p.bytes = align_up((size_t)rem * best * kBQ * dh * 4) + align_up((size_t)rem * best * kBQ * 4);
   return p;
 }
 
