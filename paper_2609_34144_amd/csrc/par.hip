@@ -48,7 +48,7 @@ __global__ __launch_bounds__(64) void par_xspec_kernel(ParArgs a, TileClass k,
 
 constexpr int kGateTargets = 8;   // targets per gate block
 constexpr int kGateWaves = 4;     // waves per gate block
-constexpr int kInlineBlocksPerCU = 7;   // resident reconstruction blocks with the gate inline
+constexpr int kInlineBlocksPerCU = 7;   // reconstruction blocks per compute unit up to which the gate is inline
 
 __global__ __launch_bounds__(64 * kGateWaves) void par_gate_kernel(ParArgs a,
                                                                     const float* __restrict__ partial,
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(64) void par_recon_kernel(ParArgs a, TileClass k,
                                                         const float* __restrict__ resid,
                                                         float* __restrict__ out,
                                                         const float4* __restrict__ coef) {
-  __shared__ float fb_lds[2 * kBins * kChb];
+  __shared__ float fb_lds[2 * kUnique * kChb];
   recon_block<HP, WP, ACC, false>(a, class_tile(a, k, blockIdx.x), blockIdx.y, blockIdx.z, resid,
                                   out, coef, fb_lds);
 }
@@ -301,16 +301,25 @@ cast_status_t launch_par(const float* resid, const int* anchors, int n_anchor, i
     const FusedRow& row = fused_row(hr > 0 ? hr : 8);
     const int wi = (wr > 0 ? wr : 8) - 1;
     const dim3 grid((unsigned)cs.end[3] * pl.n_chblk * pl.n_pairs);
+    const int cus = device_cu_count();
+    const bool debug = theta_out != nullptr || gate_out != nullptr || conf_out != nullptr;
+    // Up to kChb channels one wave holds a (tile, pair) whole, and the three passes are
+    // one launch: 4 frames of 8x8x64 21.0 -> 16.8 us, 8 of 30x52x64 25.7 -> 21.0.  Several
+    // waves per (tile, pair) in one workgroup lost: 12 frames of 44x44x128 36.3 -> 37.5,
+    // 8 of 12x12x512 33.4 -> 53.2 us (the waves of a compute unit share its instruction
+    // cache, and each runs several thousand instructions of straight-line code once).
+    if (!debug && pl.n_chblk == 1) {
+      hipLaunchKernelGGL((p.accumulate ? row.one_a[wi] : row.one_w[wi]), grid, dim3(kChb), 0, stream, a, cs,
+                         resid, out);
+      return check_launch("par_one");
+    }
     hipLaunchKernelGGL(row.xspec[wi], grid, dim3(kChb), 0, stream, a, cs, resid, partial);
     st = check_launch("par_xspec");
     if (st != CAST_OK) return st;
     // When the reconstruction grid fits in one round of resident blocks (kInlineBlocksPerCU
-    // per compute unit: the register file allows 8, LDS with the coefficients 7), each
-    // block computes its tile's gate itself, and the gate launch, a serial step of
-    // its own, goes; the debug outputs come from the gate launch.
-    const int cus = device_cu_count();
-    const bool inl = theta_out == nullptr && gate_out == nullptr && conf_out == nullptr && cus > 0 &&
-                     (long long)grid.x <= (long long)kInlineBlocksPerCU * cus;
+    // per compute unit), each block computes its tile's gate itself, and the gate launch,
+    // a serial step of its own, goes; the debug outputs come from the gate launch.
+    const bool inl = !debug && (long long)grid.x <= (long long)kInlineBlocksPerCU * cus;
     if (!inl) {
       hipLaunchKernelGGL(par_gate_kernel, gate_grid, dim3(64 * kGateWaves), 0, stream, a,
                          (const float*)partial, coef);

@@ -14,6 +14,7 @@ constexpr int kNkx = kParNkxMax;       // 5
 constexpr int kVals = kBins * 3;       // (Re Z, Im Z, W) per slot
 constexpr int kChb = 64;               // channels per block (one wave)
 constexpr int kXsStride = kChb + 2;    // LDS row of one bin slot: 64 lane values + pad (8-byte rows)
+constexpr int kUnique = 34;            // unique stored bins of an 8 x 8 tile, the most of any shape
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 struct ParArgs {
@@ -92,14 +93,14 @@ __host__ __device__ constexpr bool self_conj(int ky, int kx, int H, int W) {
 // load_tile reads the tile's HP x WP values of one channel: `r` covers the frame,
 // `tile0` is the byte offset of channel 0 of the tile's top-left token, `c4` the
 // lane's channel byte offset (always in range); fwd_tile transforms them.
-template <int HP, int WP>
+template <int HP, int WP, int AUX = 0>
 __device__ __forceinline__ void load_tile(__amdgpu_buffer_rsrc_t r, unsigned tile0, unsigned WgD4,
                                           unsigned D4, unsigned c4, float (&x)[HP][WP]) {
   fft::static_for<0, HP>([&](auto yy) {
     constexpr int y = decltype(yy)::value;
     fft::static_for<0, WP>([&](auto xx) {
       constexpr int xi = decltype(xx)::value;
-      x[y][xi] = buf_ld(r, c4, tile0 + y * WgD4 + xi * D4);
+      x[y][xi] = buf_ld<AUX>(r, c4, tile0 + y * WgD4 + xi * D4);
     });
   });
 }
@@ -145,12 +146,66 @@ __device__ __forceinline__ void fwd_tile(const float (&x)[HP][WP], float (&fr)[H
 // ---------------------------------------------------------------------------
 // par_xspec
 // ---------------------------------------------------------------------------
-// One block of the cross-spectrum pass: tile `tile`, channel block `chb`, pair.
-// Every lane transforms both anchors of its channel (all their loads in flight
-// together); the per-bin products Re(F_b conj F_a), Im(F_b conj F_a) and
-// |F_b||F_a| are summed over the 64 lanes through LDS, one quantity at a time (40
-// rows of 64 lane values plus pad, 10.6 KB, so that LDS does not limit the number
-// of resident blocks), in fixed lane order.
+// Order between one wave's LDS writes and its lanes' reads of them (LDS operations of a
+// wave complete in order; this stops the compiler from moving them).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The wave's channel sums of one (tile, channel block): the per-bin products
+// Re(F_b conj F_a), Im(F_b conj F_a) and |F_b||F_a| summed over the 64 lanes through
+// LDS, one quantity at a time (40 rows of 64 lane values plus pad, 10.6 KB, so that LDS
+// does not limit the number of resident blocks), in fixed lane order.  Value q of slot s
+// goes to dst[3 s + q].
+template <int HP, int WP>
+__device__ __forceinline__ void xspec_reduce(const float (&ar)[HP][WP / 2 + 1], const float (&ai)[HP][WP / 2 + 1],
+                                             const float (&br)[HP][WP / 2 + 1], const float (&bi)[HP][WP / 2 + 1],
+                                             float live, int lane, float* lds, float* __restrict__ dst) {
+  constexpr int NKX = WP / 2 + 1;
+  fft::static_for<0, 3>([&](auto qq) {
+    constexpr int q = decltype(qq)::value;
+    // the lane's value of quantity q at every slot (zero where no unique bin lives)
+    fft::static_for<0, kNkx * HP>([&](auto bb) {
+      constexpr int ky = decltype(bb)::value / kNkx;
+      constexpr int kx = decltype(bb)::value % kNkx;
+      constexpr int s = ky * kNkx + kx;
+      float* cell = lds + s * kXsStride + lane;
+      if constexpr (kx < NKX && ky < col_rows(kx, HP, WP)) {
+        const float xr = ar[ky][kx], xi = ai[ky][kx], yr = br[ky][kx], yi = bi[ky][kx];
+        if constexpr (q == 0) *cell = live * (yr * xr + yi * xi);
+        else if constexpr (q == 1) *cell = self_conj(ky, kx, HP, WP) ? 0.0f : live * (yi * xr - yr * xi);
+        else *cell = live * sqrtf((xr * xr + xi * xi) * (yr * yr + yi * yi));
+      } else {
+        *cell = 0.0f;
+      }
+    });
+    for (int s = HP * kNkx; s < kBins; ++s) lds[s * kXsStride + lane] = 0.0f;
+    wave_lds_order();
+    if (lane < kBins) {
+      // slot `lane`'s 64 lane values are one contiguous row: 8-byte reads, all in
+      // flight together; partial sum g takes the lanes l = g mod 4 in order
+      const f32x2* rowp = reinterpret_cast<const f32x2*>(lds + lane * kXsStride);
+      f32x2 v[kChb / 2];
+#pragma unroll
+      for (int k = 0; k < kChb / 2; ++k) v[k] = rowp[k];
+      float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
+#pragma unroll
+      for (int k = 0; k < kChb / 2; k += 2) {
+        s0 += v[k].x;
+        s1 += v[k].y;
+        s2 += v[k + 1].x;
+        s3 += v[k + 1].y;
+      }
+      dst[lane * 3 + q] = (s0 + s1) + (s2 + s3);
+    }
+    wave_lds_order();
+  });
+}
+
+// One block (one wave) of the cross-spectrum pass: tile `tile`, channel block `chb`,
+// pair.  Every lane transforms both anchors of its channel (all their loads in flight
+// together).
 template <int HP, int WP>
 __device__ __forceinline__ void xspec_block(const ParArgs& a, int tile, int chb, int pair,
                                             const float* __restrict__ resid,
@@ -173,45 +228,8 @@ __device__ __forceinline__ void xspec_block(const ParArgs& a, int tile, int chb,
     fwd_tile<HP, WP>(xb, br, bi);
   }
   const float live = valid ? 1.0f : 0.0f;   // lanes past D contribute nothing
-  float* dst = partial + (((long long)pair * a.n_tiles + tile) * a.n_chblk + chb) * kVals;
-  fft::static_for<0, 3>([&](auto qq) {
-    constexpr int q = decltype(qq)::value;
-    // the lane's value of quantity q at every slot (zero where no unique bin lives)
-    fft::static_for<0, kNkx * HP>([&](auto bb) {
-      constexpr int ky = decltype(bb)::value / kNkx;
-      constexpr int kx = decltype(bb)::value % kNkx;
-      constexpr int s = ky * kNkx + kx;
-      float* cell = lds + s * kXsStride + lane;
-      if constexpr (kx < NKX && ky < col_rows(kx, HP, WP)) {
-        const float xr = ar[ky][kx], xi = ai[ky][kx], yr = br[ky][kx], yi = bi[ky][kx];
-        if constexpr (q == 0) *cell = live * (yr * xr + yi * xi);
-        else if constexpr (q == 1) *cell = self_conj(ky, kx, HP, WP) ? 0.0f : live * (yi * xr - yr * xi);
-        else *cell = live * sqrtf((xr * xr + xi * xi) * (yr * yr + yi * yi));
-      } else {
-        *cell = 0.0f;
-      }
-    });
-    for (int s = HP * kNkx; s < kBins; ++s) lds[s * kXsStride + lane] = 0.0f;
-    __syncthreads();
-    if (lane < kBins) {
-      // slot `lane`'s 64 lane values are one contiguous row: 8-byte reads, all in
-      // flight together; partial sum g takes the lanes l = g mod 4 in order
-      const f32x2* rowp = reinterpret_cast<const f32x2*>(lds + lane * kXsStride);
-      f32x2 v[kChb / 2];
-#pragma unroll
-      for (int k = 0; k < kChb / 2; ++k) v[k] = rowp[k];
-      float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-#pragma unroll
-      for (int k = 0; k < kChb / 2; k += 2) {
-        s0 += v[k].x;
-        s1 += v[k].y;
-        s2 += v[k + 1].x;
-        s3 += v[k + 1].y;
-      }
-      dst[lane * 3 + q] = (s0 + s1) + (s2 + s3);
-    }
-    __syncthreads();
-  });
+  xspec_reduce<HP, WP>(ar, ai, br, bi, live, lane, lds,
+                       partial + (((long long)pair * a.n_tiles + tile) * a.n_chblk + chb) * kVals);
 }
 
 // ---------------------------------------------------------------------------
@@ -337,101 +355,97 @@ constexpr int unique_slot(int ky, int kx) {
   return n + ky;
 }
 
-// The anchor case of eq:block on one (tile, channel): out[f] = R_f, or += R_f.
+// The anchor case of eq:block on one (tile, channel): out[f] = R_f, or += R_f, from the
+// anchor values x that the transform has loaded, the old values all in flight together.
+// (A row of loads and stores at a time, from a second read of the anchor, the update of
+// two anchors was 8 us of a lone wave's 15 and read 173 MB more on the HY-like block.)
 // NTT: the read-modify-write of out streams (nontemporal load and store).
 template <int HP, int WP, bool ACC, bool NTT>
-__device__ __forceinline__ void anchor_tile_update(const ParArgs& a, const float* __restrict__ resid,
+__device__ __forceinline__ void anchor_tile_update(const ParArgs& a, const float (&x)[HP][WP],
                                                    float* __restrict__ out, int f, unsigned tile0,
                                                    unsigned WgD4, unsigned D4, unsigned c4) {
-  const __amdgpu_buffer_rsrc_t src = frame_rsrc(resid, f, a.frame_elems);
   const __amdgpu_buffer_rsrc_t dst = frame_rsrc(out, f, a.frame_elems);
-  fft::static_for<0, HP>([&](auto yy) {
-    constexpr int y = decltype(yy)::value;
-    float v[WP], o[WP];
-    fft::static_for<0, WP>([&](auto xx) {
-      constexpr int xi = decltype(xx)::value;
-      v[xi] = buf_ld(src, c4, tile0 + y * WgD4 + xi * D4);
-      if constexpr (ACC) o[xi] = buf_ld<NTT ? kNT : 0>(dst, c4, tile0 + y * WgD4 + xi * D4);
+  if constexpr (ACC) {
+    float o[HP][WP];
+    load_tile<HP, WP, NTT ? kNT : 0>(dst, tile0, WgD4, D4, c4, o);
+    fft::static_for<0, HP * WP>([&](auto ii) {
+      constexpr int y = decltype(ii)::value / WP, xi = decltype(ii)::value % WP;
+      buf_st<NTT ? kNT : 0>(dst, c4, tile0 + y * WgD4 + xi * D4, o[y][xi] + x[y][xi]);
     });
-    fft::static_for<0, WP>([&](auto xx) {
-      constexpr int xi = decltype(xx)::value;
-      if constexpr (ACC) buf_st<NTT ? kNT : 0>(dst, c4, tile0 + y * WgD4 + xi * D4, o[xi] + v[xi]);
-      else buf_st<kNT>(dst, c4, tile0 + y * WgD4 + xi * D4, v[xi]);
+  } else {
+    fft::static_for<0, HP * WP>([&](auto ii) {
+      constexpr int y = decltype(ii)::value / WP, xi = decltype(ii)::value % WP;
+      buf_st<kNT>(dst, c4, tile0 + y * WgD4 + xi * D4, x[y][xi]);
+    });
+  }
+}
+
+// Pair p updates its left anchor, the last pair its right one too, so every anchor slot
+// is written once (out does not overlap resid).
+template <int HP, int WP, bool ACC, bool NTT>
+__device__ __forceinline__ void update_pair_anchors(const ParArgs& a, const float (&xa)[HP][WP],
+                                                    const float (&xb)[HP][WP], float* __restrict__ out, int pair,
+                                                    unsigned tile0, unsigned WgD4, unsigned D4, unsigned c4) {
+  if (!a.update_anchors) return;
+  if (pair == a.n_anchor - 2)
+    anchor_tile_update<HP, WP, ACC, NTT>(a, xb, out, a.anchors[pair + 1], tile0, WgD4, D4, c4);
+  anchor_tile_update<HP, WP, ACC, NTT>(a, xa, out, a.anchors[pair], tile0, WgD4, D4, c4);
+}
+
+// F_b of one (tile, channel) into this lane's LDS column (LDS as extra per-lane storage:
+// no other lane reads it, so no barrier is needed).
+template <int HP, int WP>
+__device__ __forceinline__ void park_spectrum(const float (&br)[HP][WP / 2 + 1],
+                                              const float (&bi)[HP][WP / 2 + 1], float* fb_lds) {
+  static_assert(unique_bins<HP, WP>() <= kUnique, "F_b fits its LDS column");
+  fft::static_for<0, WP / 2 + 1>([&](auto kk) {
+    constexpr int kx = decltype(kk)::value;
+    fft::static_for<0, col_rows(kx, HP, WP)>([&](auto yy) {
+      constexpr int ky = decltype(yy)::value;
+      constexpr int u = unique_slot<HP, WP>(ky, kx);
+      fb_lds[(2 * u) * kChb] = br[ky][kx];
+      fb_lds[(2 * u + 1) * kChb] = bi[ky][kx];
     });
   });
 }
 
+// The lane's bin slot and its gate (lanes past the tile's bins: inactive) from the n
+// channel blocks' sums at src + j kVals, in block order.
+template <int HP, int WP>
+__device__ __forceinline__ void lane_gate(const ParArgs& a, const float* src, int n, BinSlot& bs, BinGate& bg) {
+  bs = bin_slot((int)(threadIdx.x & 63), HP, WP);
+  float zr = 0.0f, zi = 0.0f, w = 0.0f;
+  if (bs.active) {
+    src += (bs.sky * kNkx + bs.kx) * 3;
+#pragma unroll 8
+    for (int j = 0; j < n; ++j) {
+      zr += src[(long long)j * kVals + 0];
+      zi += src[(long long)j * kVals + 1];
+      w += src[(long long)j * kVals + 2];
+    }
+  }
+  bg = bin_gate(a, bs, HP, WP, zr, zi, w);
+}
+
+// The targets of one (tile, channel, pair): blend (eq:fcpasm) of F_a (registers) and F_b
+// (the lane's LDS column), inverse transforms, store or accumulate.
+//
 // NTT (accumulate mode): the targets' read-modify-write streams past the caches
 // (nontemporal loads and stores).  With several anchor pairs this pass reads every
 // interior anchor once per adjacent pair, and streaming the targets keeps those
 // anchors in the Infinity Cache for the second read.
 //
-// INL: the wave computes its tile's gate itself (bin_gate, one lane per stored bin,
-// from the cross-spectrum partials) and each target's blend coefficients into
-// coef_lds, instead of reading those of par_gate.  For grids that the chip holds
-// in one round, where the gate launch would be a serial step of its own.
-template <int HP, int WP, bool ACC, bool NTT, bool INL = false>
-__device__ __forceinline__ void recon_body(const ParArgs& a, const float* __restrict__ resid,
-                                           float* __restrict__ out,
-                                           const float4* __restrict__ coef, const TileGeom& g,
-                                           int tile, int c_lane, int pair, float* fb_lds,
-                                           const float* __restrict__ partial = nullptr,
-                                           float4* coef_lds = nullptr) {
+// INL: the blend coefficients come from the lanes' own gate (bs, bg), one bin per lane,
+// through the wave's coef_lds, instead of from par_gate.
+template <int HP, int WP, bool ACC, bool NTT, bool INL>
+__device__ __forceinline__ void recon_targets(const ParArgs& a, float* __restrict__ out,
+                                              const float4* __restrict__ coef, int tile, int pair,
+                                              unsigned tile0, unsigned WgD4, unsigned D4, unsigned c4,
+                                              const float (&ar)[HP][WP / 2 + 1],
+                                              const float (&ai)[HP][WP / 2 + 1], float* fb_lds,
+                                              const BinSlot& bs, const BinGate& bg, float4* coef_lds) {
   constexpr int NKX = WP / 2 + 1;
-  constexpr int NU = unique_bins<HP, WP>();
-  // INL: this lane's bin slot and its gate (lanes past the tile's bins: inactive)
-  BinSlot bs{};
-  BinGate bg{};
-  if constexpr (INL) {
-    bs = bin_slot((int)(threadIdx.x & 63), HP, WP);
-    float zr = 0.0f, zi = 0.0f, w = 0.0f;
-    if (bs.active) {
-      const float* src = partial + ((long long)pair * a.n_tiles + tile) * a.n_chblk * kVals +
-                         (bs.sky * kNkx + bs.kx) * 3;
-#pragma unroll 8
-      for (int j = 0; j < a.n_chblk; ++j) {
-        zr += src[(long long)j * kVals + 0];
-        zi += src[(long long)j * kVals + 1];
-        w += src[(long long)j * kVals + 2];
-      }
-    }
-    bg = bin_gate(a, bs, HP, WP, zr, zi, w);
-  }
-  // Lanes past the last channel mirror channel D-1: same inputs, same results, and
-  // they sit in the same wave as the lane that owns D-1, so their stores (and
-  // read-modify-writes) coincide with it instruction by instruction.
-  const unsigned c4 = 4u * (unsigned)(c_lane < a.D ? c_lane : a.D - 1);
-  const unsigned tile0 = 4u * (unsigned)((g.y0 * a.Wg + g.x0) * a.D);
-  const unsigned WgD4 = 4u * (unsigned)(a.Wg * a.D), D4 = 4u * (unsigned)a.D;
   const int fa = a.anchors[pair], fb = a.anchors[pair + 1];
-  if (a.update_anchors) {
-    // pair p updates its left anchor, the last pair its right one too, so every
-    // anchor slot is written once (out does not overlap resid)
-    anchor_tile_update<HP, WP, ACC, NTT>(a, resid, out, fa, tile0, WgD4, D4, c4);
-    if (pair == a.n_anchor - 2) anchor_tile_update<HP, WP, ACC, NTT>(a, resid, out, fb, tile0, WgD4, D4, c4);
-  }
-  float ar[HP][NKX], ai[HP][NKX];
-  {
-    // both anchors' loads in flight together; F_b is parked in this lane's LDS
-    // column (LDS as extra per-lane storage: no other lane reads it, so no barrier
-    // is needed)
-    float xa[HP][WP], xb[HP][WP];
-    load_tile<HP, WP>(frame_rsrc(resid, fb, a.frame_elems), tile0, WgD4, D4, c4, xb);
-    load_tile<HP, WP>(frame_rsrc(resid, fa, a.frame_elems), tile0, WgD4, D4, c4, xa);
-    float br[HP][NKX], bi[HP][NKX];
-    fwd_tile<HP, WP>(xb, br, bi);
-    fft::static_for<0, NKX>([&](auto kk) {
-      constexpr int kx = decltype(kk)::value;
-      fft::static_for<0, col_rows(kx, HP, WP)>([&](auto yy) {
-        constexpr int ky = decltype(yy)::value;
-        constexpr int u = unique_slot<HP, WP>(ky, kx);
-        fb_lds[(2 * u) * kChb] = br[ky][kx];
-        fb_lds[(2 * u + 1) * kChb] = bi[ky][kx];
-      });
-    });
-    fwd_tile<HP, WP>(xa, ar, ai);
-  }
-  (void)NU;
   const int n_pairs = a.n_anchor - 1;
   for (int part = 0; part < 3; ++part) {
     int t0, t1;
@@ -439,12 +453,12 @@ __device__ __forceinline__ void recon_body(const ParArgs& a, const float* __rest
     else if (part == 1) { if (pair != 0) continue; t0 = 0; t1 = fa; }
     else { if (pair != n_pairs - 1) continue; t0 = fb + 1; t1 = a.n_frames; }
     for (int t = t0; t < t1; ++t) {
-      const float4* __restrict__ cf = coef + ((long long)t * a.n_tiles + tile) * kBins;
+      const float4* __restrict__ cf = INL ? nullptr : coef + ((long long)t * a.n_tiles + tile) * kBins;
       if constexpr (INL) {
         // this target's coefficients, one bin per lane, into LDS for every lane
         const int b = (int)(threadIdx.x & 63);
         if (b < kBins) coef_lds[b] = blend_coef(t, fa, fb, bg.theta, bg.gate, HP, WP, bs.active);
-        __syncthreads();
+        wave_lds_order();
       }
       auto coef_at = [&](int u) -> float4 {
         if constexpr (INL) return coef_lds[u];
@@ -531,6 +545,86 @@ __device__ __forceinline__ void recon_body(const ParArgs& a, const float* __rest
   }
 }
 
+
+// INL: the wave computes its tile's gate itself (lane_gate, from the cross-spectrum
+// partials).  For grids that the chip holds in one round, where the gate launch would be
+// a serial step of its own.  (Issuing the anchors' loads before the gate was slower: 30.6
+// against 29.5 us for a call of 8 frames of 30x48x1024, 54.1 against 52.7 at 22x64x1536.)
+template <int HP, int WP, bool ACC, bool NTT, bool INL = false>
+__device__ __forceinline__ void recon_body(const ParArgs& a, const float* __restrict__ resid,
+                                           float* __restrict__ out,
+                                           const float4* __restrict__ coef, const TileGeom& g,
+                                           int tile, int c_lane, int pair, float* fb_lds,
+                                           const float* __restrict__ partial = nullptr,
+                                           float4* coef_lds = nullptr) {
+  constexpr int NKX = WP / 2 + 1;
+  // Lanes past the last channel mirror channel D-1: same inputs, same results, and
+  // they sit in the same wave as the lane that owns D-1, so their stores (and
+  // read-modify-writes) coincide with it instruction by instruction.
+  const unsigned c4 = 4u * (unsigned)(c_lane < a.D ? c_lane : a.D - 1);
+  const unsigned tile0 = 4u * (unsigned)((g.y0 * a.Wg + g.x0) * a.D);
+  const unsigned WgD4 = 4u * (unsigned)(a.Wg * a.D), D4 = 4u * (unsigned)a.D;
+  const int fa = a.anchors[pair], fb = a.anchors[pair + 1];
+  BinSlot bs{};
+  BinGate bg{};
+  auto gate = [&]() {
+    lane_gate<HP, WP>(a, partial + ((long long)pair * a.n_tiles + tile) * a.n_chblk * kVals, a.n_chblk, bs, bg);
+  };
+  if constexpr (INL) gate();
+  float ar[HP][NKX], ai[HP][NKX];
+  {
+    // both anchors' loads in flight together
+    float xa[HP][WP], xb[HP][WP];
+    load_tile<HP, WP>(frame_rsrc(resid, fb, a.frame_elems), tile0, WgD4, D4, c4, xb);
+    load_tile<HP, WP>(frame_rsrc(resid, fa, a.frame_elems), tile0, WgD4, D4, c4, xa);
+    update_pair_anchors<HP, WP, ACC, NTT>(a, xa, xb, out, pair, tile0, WgD4, D4, c4);
+    float br[HP][NKX], bi[HP][NKX];
+    fwd_tile<HP, WP>(xb, br, bi);
+    park_spectrum<HP, WP>(br, bi, fb_lds);
+    fwd_tile<HP, WP>(xa, ar, ai);
+  }
+  recon_targets<HP, WP, ACC, NTT, INL>(a, out, coef, tile, pair, tile0, WgD4, D4, c4, ar, ai, fb_lds, bs, bg,
+                                       coef_lds);
+}
+
+// One workgroup (one wave) of the one-launch reconstruction of up to kChb channels: the
+// wave holds every channel of its (tile, pair), so its own sums are the channel sums, the
+// anchors are read and transformed once, and the wave takes the gate (the same sums in
+// the same order as across two launches, so the results are bit-identical to theirs) and
+// goes on to the targets.  LDS: F_b's columns, under which the reduction's rows lie
+// first, the coefficients and the sums.
+template <int HP, int WP, bool ACC>
+__device__ __forceinline__ void one_block(const ParArgs& a, int tile, int pair, const float* __restrict__ resid,
+                                          float* __restrict__ out, float* fb_lds, float4* coef_lds, float* sums) {
+  constexpr int NKX = WP / 2 + 1;
+  const TileGeom g = tile_geom(a, tile);
+  const int lane = threadIdx.x;
+  const bool valid = lane < a.D;
+  const unsigned c4 = 4u * (unsigned)(valid ? lane : a.D - 1);
+  const unsigned tile0 = 4u * (unsigned)((g.y0 * a.Wg + g.x0) * a.D);
+  const unsigned WgD4 = 4u * (unsigned)(a.Wg * a.D), D4 = 4u * (unsigned)a.D;
+  float ar[HP][NKX], ai[HP][NKX];
+  {
+    float br[HP][NKX], bi[HP][NKX];
+    {
+      float xa[HP][WP], xb[HP][WP];
+      load_tile<HP, WP>(frame_rsrc(resid, a.anchors[pair], a.frame_elems), tile0, WgD4, D4, c4, xa);
+      load_tile<HP, WP>(frame_rsrc(resid, a.anchors[pair + 1], a.frame_elems), tile0, WgD4, D4, c4, xb);
+      update_pair_anchors<HP, WP, ACC, false>(a, xa, xb, out, pair, tile0, WgD4, D4, c4);
+      fwd_tile<HP, WP>(xa, ar, ai);
+      fwd_tile<HP, WP>(xb, br, bi);
+    }
+    static_assert(kBins * kXsStride <= 2 * kUnique * kChb, "the reduction fits under F_b");
+    xspec_reduce<HP, WP>(ar, ai, br, bi, valid ? 1.0f : 0.0f, lane, fb_lds, sums);
+    park_spectrum<HP, WP>(br, bi, fb_lds + lane);
+  }
+  BinSlot bs{};
+  BinGate bg{};
+  lane_gate<HP, WP>(a, sums, 1, bs, bg);
+  recon_targets<HP, WP, ACC, false, true>(a, out, nullptr, tile, pair, tile0, WgD4, D4, c4, ar, ai, fb_lds + lane,
+                                          bs, bg, coef_lds);
+}
+
 // One block of the reconstruction pass: tile `tile`, channel block `chb`, pair.
 template <int HP, int WP, bool ACC, bool NTT, bool INL = false>
 __device__ __forceinline__ void recon_block(const ParArgs& a, int tile, int chb, int pair,
@@ -609,7 +703,10 @@ __global__ __launch_bounds__(64) void par_recon_fused(ParArgs a, ClassSet cs,
                                                        float* __restrict__ out,
                                                        const float4* __restrict__ coef,
                                                        const float* __restrict__ partial) {
-  __shared__ float fb_lds[2 * kBins * kChb];
+  // Write mode needs fewer registers, so LDS alone holds a compute unit's blocks to seven;
+  // with nine, which the unique bins would allow, a grid of less than a round is packed
+  // onto fewer compute units (8 frames of 30x52x1536: 30.5 against 29.3 us).
+  __shared__ float fb_lds[2 * (INL && !ACC ? kBins : kUnique) * kChb];
   __shared__ float4 coef_lds[INL ? kBins : 1];
   int tile_b, chb, pair;
   fused_block_work(blockIdx.x, cs.end[3], a.n_chblk, tile_b, chb, pair);
@@ -620,6 +717,23 @@ __global__ __launch_bounds__(64) void par_recon_fused(ParArgs a, ClassSet cs,
   });
 }
 
+// One-launch reconstruction (launch_par has the rule): grid tiles x pairs, pairs in
+// recon_order.
+template <int HR, int WR, bool ACC>
+__global__ __launch_bounds__(kChb) void par_one_fused(ParArgs a, ClassSet cs, const float* __restrict__ resid,
+                                                       float* __restrict__ out) {
+  __shared__ __attribute__((aligned(16))) float fb_lds[2 * kUnique * kChb];
+  __shared__ float4 coef_lds[kBins];
+  __shared__ float sums[kVals];
+  const int ntiles = cs.end[3];
+  const int p = blockIdx.x / ntiles;
+  const int pair = a.recon_order[p];
+  for_class<HR, WR>(a, cs, blockIdx.x - p * ntiles, [&](auto hp, auto wp, int tile) {
+    one_block<decltype(hp)::value, decltype(wp)::value, ACC>(a, tile, pair, resid, out, fb_lds, coef_lds, sums);
+  });
+}
+
+typedef void (*OneFusedFn)(ParArgs, ClassSet, const float*, float*);
 typedef void (*XspecFusedFn)(ParArgs, ClassSet, const float*, float*);
 typedef void (*ReconFusedFn)(ParArgs, ClassSet, const float*, float*, const float4*, const float*);
 
@@ -629,6 +743,7 @@ struct FusedRow {
   XspecFusedFn xspec[8];
   ReconFusedFn recon_w[8], recon_a[8], recon_as[8];   // write, accumulate, accumulate streaming
   ReconFusedFn inl_w[8], inl_a[8], inl_as[8];         // the same with the gate computed inline
+  OneFusedFn one_w[8], one_a[8];                      // everything in one launch
 };
 
 void fused_row_1(FusedRow& r);

@@ -22,6 +22,8 @@ static void set_entry(FusedRow& r) {
   r.inl_w[WR - 1] = par_recon_fused<HR, WR, false, false, true>;
   r.inl_a[WR - 1] = par_recon_fused<HR, WR, true, false, true>;
   r.inl_as[WR - 1] = par_recon_fused<HR, WR, true, true, true>;
+  r.one_w[WR - 1] = par_one_fused<HR, WR, false>;
+  r.one_a[WR - 1] = par_one_fused<HR, WR, true>;
 }
 
 void CAST_CAT(fused_row_, CAST_PAR_HR)(FusedRow& r) {
