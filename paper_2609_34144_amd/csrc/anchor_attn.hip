@@ -479,6 +479,61 @@ __global__ __launch_bounds__(kThreads, wide_waves(DH)) void anchor_attn_kernel(A
   //      max (one exchange with the other half-wave), the running max moved only
   //      when the tile max exceeds it by more than kMaxSlack, exponentials again,
   //      and the O rescale.
+  auto softmax_phase = [&](int j) __attribute__((always_inline)) {
+    if (tb + j == a.nt_all - 1 && a.L != a.nt_all * kBK) {
+      const int key0 = (tb + j) * kBK;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int key = key0 + kb * 32 + 8 * (e / 4) + 4 * hf + (e % 4);
+          if (key >= a.L) sn[kb][e] = -INFINITY;
+        }
+    }
+    // row sum in fp32 over four partial sums (short dependency chains), each
+    // started from its first term (not 0 + p: the compiler keeps that add)
+    float pe[32], rs4[4];
+#pragma unroll
+    for (int e = 0; e < 32; ++e) {
+      pe[e] = __builtin_amdgcn_exp2f(fmaf(sn[e / 16][e % 16], a.sl2, -m_run));
+      rs4[e % 4] = e < 4 ? pe[e] : rs4[e % 4] + pe[e];
+    }
+    float rs = (rs4[0] + rs4[1]) + (rs4[2] + rs4[3]);
+    if (__ballot(!(rs <= kSumBound)) != 0ull) {
+      float pm = max3f(sn[0][0], sn[0][1], sn[0][2]);
+#pragma unroll
+      for (int k = 1; k < 15; ++k) {
+        const int v = 2 * k + 1;
+        pm = max3f(pm, sn[v / 16][v % 16], sn[(v + 1) / 16][(v + 1) % 16]);
+      }
+      pm = fmaxf(pm, sn[1][15]);
+      const u32x2 sw = __builtin_bit_cast(
+          u32x2, __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, pm),
+                                                  __builtin_bit_cast(unsigned, pm), false, false));
+      const float mx = fmaxf(__builtin_bit_cast(float, sw.x), __builtin_bit_cast(float, sw.y));
+      const float m_cand = fmaxf(m_run, mx * a.sl2);
+      const bool up = m_cand > m_run + kMaxSlack;
+      const float m_new = up ? m_cand : m_run;
+      const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+#pragma unroll
+      for (int e = 0; e < 32; ++e) {
+        pe[e] = __builtin_amdgcn_exp2f(fmaf(sn[e / 16][e % 16], a.sl2, -m_new));
+        rs4[e % 4] = e < 4 ? pe[e] : rs4[e % 4] + pe[e];
+      }
+      rs = (rs4[0] + rs4[1]) + (rs4[2] + rs4[3]);
+      l_run *= corr;
+      m_run = m_new;
+      if (__ballot(up) != 0ull) {
+#pragma unroll
+        for (int db = 0; db < ND; ++db) acc_o[db] *= corr;
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) pp[g / 2][g % 2] = pack8(&pe[8 * g]);
+    l_run += rs;
+  };
+  // ---- its parts in the wide schedule (the phase above keeps its own text: with these
+  //      parts in it the HY-like call was 0.3% and the long-history one 0.4% slower)
   auto mask_tail = [&](int j) __attribute__((always_inline)) {
     if (tb + j == a.nt_all - 1 && a.L != a.nt_all * kBK) {
       const int key0 = (tb + j) * kBK;
@@ -515,30 +570,6 @@ __global__ __launch_bounds__(kThreads, wide_waves(DH)) void anchor_attn_kernel(A
       for (int db = 0; db < ND; ++db) acc_o[db] *= corr;
     }
     return m_new;
-  };
-  auto softmax_phase = [&](int j) __attribute__((always_inline)) {
-    mask_tail(j);
-    // row sum in fp32 over four partial sums (short dependency chains), each
-    // started from its first term (not 0 + p: the compiler keeps that add)
-    float pe[32], rs4[4];
-#pragma unroll
-    for (int e = 0; e < 32; ++e) {
-      pe[e] = __builtin_amdgcn_exp2f(fmaf(sn[e / 16][e % 16], a.sl2, -m_run));
-      rs4[e % 4] = e < 4 ? pe[e] : rs4[e % 4] + pe[e];
-    }
-    float rs = (rs4[0] + rs4[1]) + (rs4[2] + rs4[3]);
-    if (__ballot(!(rs <= kSumBound)) != 0ull) {
-      m_run = move_max();
-#pragma unroll
-      for (int e = 0; e < 32; ++e) {
-        pe[e] = __builtin_amdgcn_exp2f(fmaf(sn[e / 16][e % 16], a.sl2, -m_run));
-        rs4[e % 4] = e < 4 ? pe[e] : rs4[e % 4] + pe[e];
-      }
-      rs = (rs4[0] + rs4[1]) + (rs4[2] + rs4[3]);
-    }
-#pragma unroll
-    for (int g = 0; g < 4; ++g) pp[g / 2][g % 2] = pack8(&pe[8 * g]);
-    l_run += rs;
   };
   // the same in the wide schedule, the exponentials in place of the scores (a second
   // set would cost the registers of two waves per SIMD): the exact path, which needs
