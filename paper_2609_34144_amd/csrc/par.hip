@@ -66,13 +66,7 @@ __global__ __launch_bounds__(64 * kGateWaves) void par_gate_kernel(ParArgs a,
     if (bs.active) {
       const float* src = partial + ((long long)pair * a.n_tiles + tile) * a.n_chblk * kVals +
                          (bs.sky * kNkx + bs.kx) * 3;
-      const int j0 = a.n_chblk * wv / kGateWaves, j1 = a.n_chblk * (wv + 1) / kGateWaves;
-#pragma unroll 4
-      for (int j = j0; j < j1; ++j) {
-        zr += src[(long long)j * kVals + 0];
-        zi += src[(long long)j * kVals + 1];
-        w += src[(long long)j * kVals + 2];
-      }
+      sum_blocks(src, a.n_chblk * wv / kGateWaves, a.n_chblk * (wv + 1) / kGateWaves, zr, zi, w);
     }
     part[wv][0][b] = zr;
     part[wv][1][b] = zi;

@@ -409,6 +409,32 @@ __device__ __forceinline__ void park_spectrum(const float (&br)[HP][WP / 2 + 1],
   });
 }
 
+// Sums of channel blocks [j0, j1) of one slot (src + j kVals), in block order, eight
+// blocks' loads in flight together; blocks past j1 read the last one and add nothing.
+// (As a loop unrolled by eight, the blocks past a multiple of eight went one load at a
+// time: 8 frames of 30x48x448 26.8 -> 25.3 us, of 30x48x960 25.8 -> 24.3; multiples of
+// eight within 1%.)
+__device__ __forceinline__ void sum_blocks(const float* src, int j0, int j1, float& zr, float& zi, float& w) {
+  constexpr int N = 8;
+  for (int j = j0; j < j1; j += N) {
+    float v[N][3];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const float* p = src + (long long)min(j + u, j1 - 1) * kVals;
+      v[u][0] = p[0];
+      v[u][1] = p[1];
+      v[u][2] = p[2];
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const bool in = j + u < j1;
+      zr += in ? v[u][0] : 0.0f;
+      zi += in ? v[u][1] : 0.0f;
+      w += in ? v[u][2] : 0.0f;
+    }
+  }
+}
+
 // The lane's bin slot and its gate (lanes past the tile's bins: inactive) from the n
 // channel blocks' sums at src + j kVals, in block order.
 template <int HP, int WP>
@@ -416,13 +442,7 @@ __device__ __forceinline__ void lane_gate(const ParArgs& a, const float* src, in
   bs = bin_slot((int)(threadIdx.x & 63), HP, WP);
   float zr = 0.0f, zi = 0.0f, w = 0.0f;
   if (bs.active) {
-    src += (bs.sky * kNkx + bs.kx) * 3;
-#pragma unroll 8
-    for (int j = 0; j < n; ++j) {
-      zr += src[(long long)j * kVals + 0];
-      zi += src[(long long)j * kVals + 1];
-      w += src[(long long)j * kVals + 2];
-    }
+    sum_blocks(src + (bs.sky * kNkx + bs.kx) * 3, 0, n, zr, zi, w);
   }
   bg = bin_gate(a, bs, HP, WP, zr, zi, w);
 }
