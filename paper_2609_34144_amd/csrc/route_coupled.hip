@@ -93,7 +93,9 @@ __global__ __launch_bounds__(kThreads) void coupled_scores_kernel(CoupledArgs a)
     const bool in = lane < nm;
     if (in) a.scores[ih * a.M + m0 + lane] = sc;
     const float mx = wave_max(in ? sc : -INFINITY);
-    const float e = in ? expf(sc - mx) : 0.0f;
+    // a score of -inf adds nothing, also where the tile has no other (-inf - mx would be
+    // NaN there, and the tile's weight of 0 in the merge would not remove it)
+    const float e = in && sc != -INFINITY ? expf(sc - mx) : 0.0f;
     const float sum = wave_sum(e);
     tile[tid] = e;
     if (lane == 0) {
