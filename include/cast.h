@@ -208,7 +208,7 @@ cast_status_t cast_route_coupled(const void* q, const void* k_hist, const void* 
  * lse_out  fp32 [n_a, H, S] device natural-log sum of exp of the scaled logits,
  *          or NULL to skip.
  * workspace  device scratch, or NULL.  The work is n_a * H * ceil(S / 256) units
- *          (anchor, head, 256-query tile).  With a workspace, the units of a last
+ *          (anchor, head, 256-query tile).  With a workspace, units of a last
  *          partial round on the device's compute units run as 2..16 pieces over
  *          disjoint key ranges where that is sooner, and are merged (the softmax of each
  *          piece renormalised by its log-sum-exp), which shortens that round;

@@ -34,6 +34,8 @@
 //                 LDS load ds_read_b64_tr_b16.
 // Blocks are renumbered so that the Q-tiles of one (anchor, head) land on the
 // same XCD and share its L2 for the routed K/V.
+#include <algorithm>
+
 #include "cast_common.h"
 
 namespace cast {
@@ -780,31 +782,48 @@ cast_status_t launch_dh(AttnArgs a, hipStream_t stream) {
 
 }  // namespace
 
-// The last U mod C units of a grid of C resident workgroups run as s pieces along the
-// keys when that is estimated to be sooner: a piece takes ceil(tiles / s) tile times
-// (measured per 64-key tile: 1.65 us at dh = 128 with one workgroup per compute unit;
-// 1.3 / 2.05 us at dh = 64 and 1.0 / 1.6 us at dh = 32 with one / two), and the split
-// adds the merge launch (4 us) and the pieces' fp32 partials, written and read once
-// (4.5 TB/s).  Measured: 96 units of 11 tiles 23.1 us whole and 27.0 in two pieces, of
-// 22 tiles 35.7 and 32.9; 32 units of 39 tiles 46.6 in two pieces and 29.5 in eight;
-// dh = 64, 240 units of 33 tiles 47.7 whole and 54.5 in two pieces.
+// Key split of the last U mod C units of a grid of C resident workgroups.
+//
+// Fewer left than compute units: as many pieces as an estimate finds soonest.  A piece
+// takes ceil(tiles / s) tile times (us per 64-key tile with one workgroup on a compute
+// unit, and with two); the split adds the merge launch, which walks the s pieces, and the
+// fp32 partials, cheap past the first 108 pieces of 256 x 128 (14 MB), dear again where
+// they fill the L2s (256 pieces, 33.5 MB).  Behind whole rounds the launch is part hidden.
+// The constants are a fit to 5000 timed plans of 950 shapes (2 to 1584 units, 1 to 500
+// tiles): within 3% of the best plan timed on nine shapes in ten.  Those of long runs on
+// the full chip (1.65 us a tile at dh = 128) split too soon: 64 units of 14 tiles 27.2 us
+// whole and 31.3 so, of 48 tiles 41.3 in three pieces and 47.2 in four.
+//
+// More left than compute units (two workgroups each, dh <= 64): the pieces would not fit
+// beside each other, and left whole, the few units past one per compute unit hold the
+// launch at the rate of two per unit throughout.  So only those few are split, into
+// pieces of at least 16 tiles, at most 8 and no more than compute units.  dh = 64, 276
+// units of 64 tiles 118.7 us whole and 89.2 as 256 + 20 in four pieces; of 98 tiles 178
+// and 130; 384 units of 33 tiles 69.2 and 66.4; dh = 32, 264 of 98 tiles 141 and 99.
 AttnSplitPlan attn_split_plan(int n_a, int S, int H, int dh, long long L, int cus) {
   constexpr long long kMaxSplit = 16, kMinPieceTiles = 2;
   const long long units = (long long)n_a * H * ((S + kBQ - 1) / kBQ);
   AttnSplitPlan p{(int)units, 0, 1, 0};
   if (cus <= 0) return p;
   const int per_cu = wide_waves(dh) / 2;
-  const long long slots = (long long)cus * per_cu, rem = units % slots;
+  const long long slots = (long long)cus * per_cu, nt_all = (L + kBK - 1) / kBK;
+  long long rem = units % slots, best = 1;
   if (rem == 0) return p;
-  const long long nt_all = (L + kBK - 1) / kBK;
-  const double tile_us[2] = {dh == 128 ? 1.65 : dh == 64 ? 1.3 : 1.0, dh == 64 ? 2.05 : 1.6};
-  auto estimate = [&](long long s) {
-    const double run = (double)((nt_all + s - 1) / s) * tile_us[rem * s > cus ? 1 : 0];
-    return s == 1 ? run : run + 4.0 + (double)(rem * s * kBQ * dh) * 8.0 / 4.5e6;
-  };
-  long long best = 1;
-  for (long long s = 2; s <= kMaxSplit && rem * s <= slots && s * kMinPieceTiles <= nt_all; ++s)
-    if (estimate(s) < estimate(best)) best = s;
+  if (rem > cus) {
+    rem -= cus;
+    best = std::min({8ll, cus / rem, nt_all / 16});
+  } else {
+    const double tile_us[2] = {dh == 128 ? 1.08 : dh == 64 ? 1.06 : 0.82, dh == 64 ? 1.83 : 1.18};
+    auto estimate = [&](long long s) {
+      const double run = (double)((nt_all + s - 1) / s) * tile_us[rem * s > cus ? 1 : 0];
+      if (s == 1) return run;
+      const double full = (double)(rem * s * dh) / 128;   // in pieces of 256 x 128
+      return run + (units > slots ? 0.3 : 2.1) + 0.38 * (double)s + 0.067 * std::min(full, 108.0) +
+             0.028 * std::max(full - 108.0, 0.0) + (full > 240 ? 3.3 : 0.0);
+    };
+    for (long long s = 2; s <= kMaxSplit && rem * s <= slots && s * kMinPieceTiles <= nt_all; ++s)
+      if (estimate(s) < estimate(best)) best = s;
+  }
   if (best < 2) return p;
   p.n_full = (int)(units - rem);
   p.n_split = (int)rem;

@@ -50,3 +50,21 @@ def test_scores_formed_again(cast_lib, dh):
     idx[:] = torch.arange(8, device="cuda", dtype=torch.int32)
     k *= torch.tensor([0.05, 4, 0.5, 8, 1, 12, 0.1, 6], device="cuda")[:, None, None, None].to(torch.bfloat16)
     check_attn(cast_lib, q, k, v, idx, 8, 1 / math.sqrt(dh), kc=kc, vc=vc, label=f"exact path dh{dh}")
+
+
+@pytest.mark.parametrize("dh", [32, 64])
+@pytest.mark.parametrize("n_a,S,H,M,Bv,k_eff,n0", [
+    (2, 40, 138, 40, 64, 34, 0),     # 256 whole units of one tile, 20 in pieces, aligned chunks
+    (2, 300, 67, 12, 200, 11, 90),   # two tiles each, 12 units in pieces, a segment, ragged tails
+])
+def test_whole_units_beside_pieces(cast_lib, dh, n_a, S, H, M, Bv, k_eff, n0):
+    """Whole units on every compute unit and the few past them split along the keys, in
+    one launch: sampled queries of the first, middle and last (anchor, head) pairs."""
+    assert cast_lib.cast_anchor_attn_workspace_bytes(n_a, S, H, dh, k_eff, n0, Bv) > 0
+    q, k, v, idx, kc, vc = _inputs(n_a, S, H, dh, M, Bv, k_eff, n0, S + dh)
+    rows = [(i, h, s) for i, h in ((0, 0), (0, H // 2), (0, H - 1), (1, 0), (1, H - 20), (1, H - 6), (1, H - 2), (1, H - 1))
+            for s in (0, 31, S // 2, S - 1)]
+    outs = [check_attn(cast_lib, q, k, v, idx, k_eff, 1 / math.sqrt(dh), kc=kc, vc=vc, rows=rows, split=split,
+                       label=f"whole + pieces dh{dh} S{S} split {split}") for split in (True, False)]
+    d = (outs[0].float() - outs[1].float()).abs().max().item()
+    assert d <= 2.0 ** -7 * max(1.0, outs[1].float().abs().max().item())
