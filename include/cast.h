@@ -214,8 +214,10 @@ cast_status_t cast_route_coupled(const void* q, const void* k_hist, const void* 
  *          piece renormalised by its log-sum-exp), which shortens that round;
  *          results agree with the unsplit run to fp32 rounding before the bf16
  *          output.  A non-NULL workspace must be 256-byte aligned and hold
- *          cast_anchor_attn_workspace_bytes(...) bytes (CAST_ERR_WORKSPACE
- *          otherwise); NULL runs every unit whole.  Owned by the caller; its
+ *          cast_anchor_attn_workspace_bytes(...) bytes where the call splits
+ *          (CAST_ERR_WORKSPACE otherwise); NULL runs every unit whole.  That size
+ *          does not fall as n0 + k_eff*Bv grows with the other sizes fixed: one
+ *          for the longest history serves every shorter one.  Owned by the caller; its
  *          contents need no initialisation and are garbage after the call.
  */
 cast_status_t cast_anchor_attn(const void* q, const void* k_hist, const void* v_hist,

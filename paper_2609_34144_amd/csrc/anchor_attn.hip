@@ -800,6 +800,10 @@ cast_status_t launch_dh(AttnArgs a, hipStream_t stream) {
 // pieces of at least 16 tiles, at most 8 and no more than compute units.  dh = 64, 276
 // units of 64 tiles 118.7 us whole and 89.2 as 256 + 20 in four pieces; of 98 tiles 178
 // and 130; 384 units of 33 tiles 69.2 and 66.4; dh = 32, 264 of 98 tiles 141 and 99.
+//
+// The soonest piece count falls here and there as tiles are added (the last piece fills
+// up), but a caller with a growing history keeps one workspace: its size is that of the
+// most pieces any sequence up to this length could take, so it never falls.
 AttnSplitPlan attn_split_plan(int n_a, int S, int H, int dh, long long L, int cus) {
   constexpr long long kMaxSplit = 16, kMinPieceTiles = 2;
   const long long units = (long long)n_a * H * ((S + kBQ - 1) / kBQ);
@@ -807,28 +811,34 @@ AttnSplitPlan attn_split_plan(int n_a, int S, int H, int dh, long long L, int cu
   if (cus <= 0) return p;
   const int per_cu = wide_waves(dh) / 2;
   const long long slots = (long long)cus * per_cu, nt_all = (L + kBK - 1) / kBK;
-  long long rem = units % slots, best = 1;
+  long long rem = units % slots, best = 1, reserve = 1;
   if (rem == 0) return p;
   if (rem > cus) {
     rem -= cus;
-    best = std::min({8ll, cus / rem, nt_all / 16});
+    best = reserve = std::min({8ll, cus / rem, nt_all / 16});
   } else {
     const double tile_us[2] = {dh == 128 ? 1.08 : dh == 64 ? 1.06 : 0.82, dh == 64 ? 1.83 : 1.18};
-    auto estimate = [&](long long s) {
-      const double run = (double)((nt_all + s - 1) / s) * tile_us[rem * s > cus ? 1 : 0];
-      if (s == 1) return run;
+    auto tiles_us = [&](double tiles, long long s) { return tiles * tile_us[rem * s > cus ? 1 : 0]; };
+    auto split_us = [&](long long s) {
+      if (s == 1) return 0.0;
       const double full = (double)(rem * s * dh) / 128;   // in pieces of 256 x 128
-      return run + (units > slots ? 0.3 : 2.1) + 0.38 * (double)s + 0.067 * std::min(full, 108.0) +
+      return (units > slots ? 0.3 : 2.1) + 0.38 * (double)s + 0.067 * std::min(full, 108.0) +
              0.028 * std::max(full - 108.0, 0.0) + (full > 240 ? 3.3 : 0.0);
     };
-    for (long long s = 2; s <= kMaxSplit && rem * s <= slots && s * kMinPieceTiles <= nt_all; ++s)
+    auto estimate = [&](long long s) { return tiles_us((double)((nt_all + s - 1) / s), s) + split_us(s); };
+    for (long long s = 2; s <= kMaxSplit && rem * s <= slots && s * kMinPieceTiles <= nt_all; ++s) {
       if (estimate(s) < estimate(best)) best = s;
+      // sooner than whole at this many tiles or, if it ever was, at fewer (without the
+      // rounding up, what s saves only grows with the tiles)
+      if (tiles_us((double)nt_all / (double)s, s) + split_us(s) < tiles_us((double)nt_all, 1)) reserve = s;
+    }
   }
+  if (reserve >= 2)
+    p.bytes = align_up((size_t)rem * reserve * kBQ * dh * 4) + align_up((size_t)rem * reserve * kBQ * 4);
   if (best < 2) return p;
   p.n_full = (int)(units - rem);
   p.n_split = (int)rem;
   p.split = (int)best;
-  p.bytes = align_up((size_t)rem * best * kBQ * dh * 4) + align_up((size_t)rem * best * kBQ * 4);
   return p;
 }
 

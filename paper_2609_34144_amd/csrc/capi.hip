@@ -256,7 +256,7 @@ cast_status_t cast_anchor_attn(const void* q, const void* k_hist, const void* v_
     if (!aligned(workspace, kWsAlign))
       return fail(CAST_ERR_WORKSPACE, "attn: workspace must be %zu-byte aligned", kWsAlign);
     plan = attn_split_plan(n_a, S, H, dh, L, device_cu_count());
-    if (workspace_bytes < plan.bytes)
+    if (plan.n_split > 0 && workspace_bytes < plan.bytes)
       return fail(CAST_ERR_WORKSPACE, "attn: workspace has %zu bytes, %zu needed", workspace_bytes, plan.bytes);
   }
   return launch_anchor_attn(q, k_hist, v_hist, idx, k_eff, k_cur, v_cur, n0, n_a, S, H, dh, M,

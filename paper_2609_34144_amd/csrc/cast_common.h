@@ -78,8 +78,8 @@ constexpr int kAttnMaxKeff = 1024;   // routed chunks per (anchor, head)
 // unit at dh = 128, two below), the last U mod C units (all of them when U < C) form a
 // partial round; when that is estimated to be sooner they, or where they are more than
 // compute units those past one per compute unit, run as `split` pieces over disjoint key
-// ranges (at most 16, each at least 2 key tiles, no more than one round in all), which
-// the pieces' partial outputs need `bytes` of workspace for.
+// ranges (at most 16, each at least 2 key tiles, no more than one round in all).  `bytes`
+// of workspace hold the partial outputs of this plan and of any shorter sequence's.
 struct AttnSplitPlan {
   int n_full, n_split, split;
   size_t bytes;

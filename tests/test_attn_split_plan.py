@@ -62,3 +62,17 @@ def test_pieces_fit_the_grid(plan):
         assert 2 <= p.split <= 16 and 2 * p.split <= tiles and p.n_split * p.split <= slots
         assert p.n_full % CUS == 0
         assert p.bytes >= p.n_split * p.split * 256 * (dh + 1) * 4
+
+
+def test_workspace_never_falls_as_the_history_grows(plan):
+    """A workspace sized for the longest history serves every shorter one."""
+    rng = np.random.default_rng(1)
+    shapes = [(128, 64), (32, 64), (64, 16)] + [
+        (int(rng.choice([32, 64, 128])), int(np.exp(rng.uniform(0, 7.5)))) for _ in range(400)]
+    for dh, units in shapes:
+        size = 0
+        for tiles in list(range(1, 200)) + [256, 300, 500, 511, 512, 1000, 5000]:
+            p = plan(units, dh, tiles)
+            assert p.bytes >= size, (dh, units, tiles)
+            assert p.bytes >= p.n_split * p.split * 256 * (dh + 1) * 4
+            size = p.bytes

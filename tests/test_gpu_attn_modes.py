@@ -68,3 +68,17 @@ def test_whole_units_beside_pieces(cast_lib, dh, n_a, S, H, M, Bv, k_eff, n0):
                        label=f"whole + pieces dh{dh} S{S} split {split}") for split in (True, False)]
     d = (outs[0].float() - outs[1].float()).abs().max().item()
     assert d <= 2.0 ** -7 * max(1.0, outs[1].float().abs().max().item())
+
+
+@pytest.mark.parametrize("dh", [32, 64, 128])
+def test_longest_historys_workspace_serves_shorter_ones(cast_lib, dh):
+    """A loop that allocates once for its longest history: every shorter call is accepted
+    and is bit-identical to the same call with a workspace of its own size."""
+    n_a, S, H, Bv = 2, 256, 8, 64
+    q, k, v, idx, _, _ = _inputs(n_a, S, H, dh, 64, Bv, 64, 0, dh)
+    ws = torch.empty(cast_lib.cast_anchor_attn_workspace_bytes(n_a, S, H, dh, 64, 0, Bv), dtype=torch.uint8, device="cuda")
+    for k_eff in range(64, 0, -1):
+        sub = idx[:, :, :k_eff].contiguous()
+        a, _ = cast_lib.cast_anchor_attn(q, k, v, sub, k_eff, 0.1, workspace=ws)
+        b, _ = cast_lib.cast_anchor_attn(q, k, v, sub, k_eff, 0.1)
+        assert torch.equal(a, b), k_eff
