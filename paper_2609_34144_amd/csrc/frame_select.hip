@@ -11,7 +11,8 @@
 //               the chunk, the normalised responses and their mean d_i; ages after
 //               the block's anchors, coverage debt h_i / ceil(N / K_f), score
 //               d_i + lambda D_i (lambda D_i without a fresh response); the K_f
-//               best frames by counting (topk_select.h) under (score descending, frame
+//               best frames (by rank, above kRankFrames by the counting TopK of
+//               topk_select.h) under (score descending, frame
 //               ascending), written in ascending frame order.  Every float operation after r is one
 //               correctly rounded fp32 operation (no contraction), so the
 //               decision is reproducible on the host in fp32.
@@ -26,6 +27,7 @@ constexpr int kSqThreads = 256;
 constexpr int kSpan = 32768;          // elements per partial (128 per thread)
 constexpr int kUnroll = 4;            // independent 16-byte loads in flight per thread
 constexpr int kSelThreads = 1024;
+constexpr int kRankFrames = 512;      // frames up to which every frame is ranked among all
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -168,14 +170,19 @@ __device__ __forceinline__ void choose_frames(const SelArgs& a, const float (&sc
 
 // Bound by latency: the partials' loads, then a chain of small reductions.  Up to 64
 // frames (every chunk in use) the first wave finishes alone, one frame per lane, with
-// no barrier after the sums; more frames take all 16 waves.  16 frames of
-// 44x80x3072 in two branches: 9.6 -> 7.5 us (half of it the 330 partials per frame); a
-// call of 8 frames of 30x52x1536 19.1 -> 18.2, of 300 frames 48 -> 31, of 4096 1193 ->
-// 210 us (the ranks were counted over all frames, the positions from one by one).
+// no barrier after the sums.  Up to kRankFrames a thread ranks its frame among all, one
+// comparison per pair; the counting TopK, whose 16 exchanges between 16 waves take 10 us
+// whatever the number of frames, takes over where the ranks cost as much.  Device times
+// without a branch, ranked and counted: 65 frames 4.0 and 15.1 us, 256 5.9 and 15.6, 512
+// 9.1 and 15.7; with one branch 512 23.2 and 27.2, 600 27.0 and 27.4, 700 30.6 and 29.3;
+// 4096 frames counted 16 us, and 620 ranked with two comparisons per pair and positions
+// counted one by one.  16 frames of 44x80x3072 in two branches: 9.6 -> 7.5 us (half of it
+// the 330 partials per frame).
 __global__ __launch_bounds__(kSelThreads) void frame_select_kernel(SelArgs a) {
   __shared__ float r[2][kSelectMaxFrames];
   __shared__ float red[2][kSelThreads / 64];
   __shared__ sel::Scratch scratch;
+  __shared__ __attribute__((aligned(16))) float scores[kRankFrames];
   const int tid = threadIdx.x, n = a.n_cur;
   const int wave = tid >> 6, lane = tid & 63;
   // r per present branch: half a wave per (branch, frame) adds its partials in fp64,
@@ -240,6 +247,38 @@ __global__ __launch_bounds__(kSelThreads) void frame_select_kernel(SelArgs a) {
     }
     __syncthreads();
   }
+  auto score_of = [&](int i) {
+    const float ri[2] = {a.n_present > 0 ? r[0][i] : 0.0f, a.n_present > 1 ? r[1][i] : 0.0f};
+    return frame_score(a, i, a.ages[i], ri, lo, hi);
+  };
+  if (n <= kRankFrames) {
+    // thread i ranks frame i among all; the scores past the last beat nothing
+    float* sc = scores;
+    const float si = tid < n ? score_of(tid) : -INFINITY;
+    if (tid < kRankFrames) sc[tid] = si;
+    __syncthreads();
+    // frames before the wave's own beat its frames when equal, later ones do not
+    const f32x4* s4 = reinterpret_cast<const f32x4*>(sc);
+    const int w0 = __builtin_amdgcn_readfirstlane(wave * 64);
+    int rank = 0;
+    auto count = [&](int j0, int j1, auto beats) {
+#pragma unroll 4
+      for (int j = j0; j < j1; j += 4) {
+        const f32x4 v = s4[j / 4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) rank += beats(v[e], j + e) ? 1 : 0;
+      }
+    };
+    if (w0 < n) {
+      count(0, w0, [&](float v, int) { return v >= si; });
+      count(w0, min(w0 + 64, n), [&](float v, int j) { return (v > si) | ((v == si) & (j < tid)); });
+      count(w0 + 64, n, [&](float v, int) { return v > si; });
+    }
+    const unsigned long long win[1] = {__ballot(tid < n && rank < a.k_f)};
+    int par = 0;
+    sel::write_indices<kSelThreads / 64, 1>(win, scratch, par, a.anchors_out, a.k_f);
+    return;
+  }
   constexpr int KPT = kSelectMaxFrames / kSelThreads;
   float sc[KPT];
   bool in[KPT];
@@ -247,11 +286,7 @@ __global__ __launch_bounds__(kSelThreads) void frame_select_kernel(SelArgs a) {
   for (int j = 0; j < KPT; ++j) {
     const int i = (wave * KPT + j) * 64 + lane;
     in[j] = i < n;
-    sc[j] = 0.0f;
-    if (in[j]) {
-      const float ri[2] = {a.n_present > 0 ? r[0][i] : 0.0f, a.n_present > 1 ? r[1][i] : 0.0f};
-      sc[j] = frame_score(a, i, a.ages[i], ri, lo, hi);
-    }
+    sc[j] = in[j] ? score_of(i) : 0.0f;
   }
   choose_frames<kSelThreads / 64, KPT>(a, sc, in, scratch);
 }

@@ -1,5 +1,5 @@
-"""Frame selection at the edges of its selection paths (one wave up to 64 frames, all
-waves above, four frames per lane at 4096), with the checker and the bars of
+"""Frame selection at the edges of its selection paths (one wave up to 64 frames, ranks
+to 512, counting in all waves above, four frames per lane at 4096), with the checker and the bars of
 test_gpu_frame_select, and its order on scores that are not numbers."""
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ from test_gpu_frame_select import one_step
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 2, 32, 33, 63, 64, 65, 1024, 1025, 4096])
+@pytest.mark.parametrize("n", [1, 2, 32, 33, 63, 64, 65, 128, 131, 511, 512, 513, 1024, 1025, 4096])
 @pytest.mark.parametrize("branches", [0, 1, 2])
 def test_edges(cast_lib, n, branches):
     g = torch.Generator(device="cuda")
@@ -25,7 +25,7 @@ def test_edges(cast_lib, n, branches):
                  f"n{n} k{k_f} b{branches}", n_cur=n)
 
 
-@pytest.mark.parametrize("n", [12, 100])
+@pytest.mark.parametrize("n", [12, 100, 600])
 def test_nan_scores_are_chosen_first_come(cast_lib, n):
     """A NaN score is neither beaten nor beats: the frames that hold one are chosen with
     the K_f best of the others, and the first K_f of all chosen are written."""
