@@ -7,8 +7,8 @@
 // mask and words follow each other in ascending index order.  The k-th largest key
 // is found from its top bit down by counting the keys at or above a candidate
 // (ballots and popcounts), and the walk ends early once a candidate keeps exactly k.
-// One wave walks bit by bit with no barrier; several waves take two bits per step,
-// one LDS exchange of packed counts each.  Everything is integer work: results do
+// One wave walks bit by bit with no barrier (up to kRankN values it ranks them instead);
+// several waves take two bits per step, one LDS exchange of packed counts each.  Everything is integer work: results do
 // not depend on the schedule.
 #pragma once
 
@@ -69,6 +69,30 @@ __device__ __forceinline__ void wave_prefix(int mine, Scratch& s, int& par, int&
   }
 }
 
+// Few values in one wave, one per lane (lanes 0 .. n - 1): each lane counts the larger
+// keys, and where equals straddle the k-th place the lower lanes take it.  A walk has the
+// keys' common leading bits to pass first, and all 32 where equals straddle: routing's
+// call over 2 chunks, 4 anchors, 12 heads of 128 7.3 us of device time ranked and 7.75
+// walked, over 32 chunks 8.0 and 8.2, over 48 8.16 and 8.07, over 64 9.7 and 9.4; frame
+// selection by age alone 2.1 and 3.5 us at 4 frames, 3.0 and 3.6 at 40.  Keeping every
+// value, the walk ends at its first bit.
+constexpr int kRankN = 40;
+__device__ __forceinline__ void rank_word(uint32_t key, bool valid, int n, int k, unsigned long long& win) {
+  int above = 0;
+  for (int j = 0; j < n; j += 8) {   // (lanes past n hold key 0)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) above += (uint32_t)__builtin_amdgcn_readlane((int)key, j + u) > key ? 1 : 0;
+  }
+  win = __ballot(valid && above < k);
+  if (__popcll(win) <= k) return;
+  int last = valid && above < k ? above : -1;   // the place of the equals
+  for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o));
+  const unsigned long long eq = __ballot(valid && above == last);
+  const int lane = threadIdx.x & 63;
+  const bool in = above < last || (above == last && __popcll(eq & ((1ull << lane) - 1ull)) < k - last);
+  win = __ballot(valid && in);
+}
+
 // Winner words of this wave's slots: win[j] bit l set when the value at (wave, j, l)
 // is among the k largest.  Slots past the n values carry key 0 and valid = false;
 // 1 <= k <= n.  `par` counts the group's exchanges, which take their LDS
@@ -76,6 +100,13 @@ __device__ __forceinline__ void wave_prefix(int mine, Scratch& s, int& par, int&
 template <int NW, int KPT>
 __device__ __forceinline__ void topk_words(const uint32_t (&key)[KPT], const bool (&valid)[KPT], int k,
                                            Scratch& s, int& par, unsigned long long (&win)[KPT]) {
+  if constexpr (NW == 1 && KPT == 1) {
+    const int n = 64 - __clzll(__ballot(valid[0]));
+    if (n <= kRankN && k < n) {
+      rank_word(key[0], valid[0], n, k, win[0]);
+      return;
+    }
+  }
   uint32_t t = 0;
   bool exact = false;
   int above = 0;   // values strictly above t once the walk ends without `exact`

@@ -18,7 +18,7 @@ def _workload(H, dh, anchors):
     return W.Workload(**{**gen.get(W.TINY).__dict__, "H": H, "dh": dh, "anchors": tuple(anchors)})
 
 
-@pytest.mark.parametrize("M", [1, 2, 63, 64, 65, 127, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096])
+@pytest.mark.parametrize("M", [1, 2, 40, 41, 63, 64, 65, 127, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096])
 def test_solver_edges(cast_lib, M):
     w = _workload(2, 32, (1, 4, 6))
     (exact, loose), idx = run_case(cast_lib, w, w.anchors, 9, max(1, M // 6), M=M, Bv=2, seed=M)

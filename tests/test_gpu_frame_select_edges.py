@@ -10,7 +10,7 @@ from test_gpu_frame_select import one_step
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 2, 32, 33, 63, 64, 65, 128, 131, 511, 512, 513, 1024, 1025, 4096])
+@pytest.mark.parametrize("n", [1, 2, 32, 33, 40, 41, 63, 64, 65, 128, 131, 511, 512, 513, 1024, 1025, 4096])
 @pytest.mark.parametrize("branches", [0, 1, 2])
 def test_edges(cast_lib, n, branches):
     g = torch.Generator(device="cuda")

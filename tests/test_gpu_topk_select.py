@@ -1,5 +1,5 @@
-"""TopK selection of cast_route_kv at the edges of its kernels (64, 256 and 512 chunks in
-one launch by keys per lane, 1024, 2048 and 4096 in two): one token per frame and chunk
+"""TopK selection of cast_route_kv at the edges of its kernels (ranks up to 40 chunks; 64, 256 and
+512 in one launch by keys per lane, 1024, 2048 and 4096 in two): one token per frame and chunk
 with small integer channels makes every score an exact integer in fp32, so the selection
 has many exact ties and must equal the order (score descending, index ascending) with no
 tolerance."""
@@ -11,7 +11,7 @@ import oracle.route
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M", [1, 2, 63, 64, 65, 255, 256, 257, 511, 512, 513, 1024, 1025, 2048, 2049, 4095, 4096])
+@pytest.mark.parametrize("M", [1, 2, 7, 8, 9, 40, 41, 63, 64, 65, 255, 256, 257, 511, 512, 513, 1024, 1025, 2048, 2049, 4095, 4096])
 @pytest.mark.parametrize("dh,H,n_a", [(32, 3, 1), (64, 2, 5), (128, 1, 4)])
 def test_selection_at_kernel_edges(cast_lib, dh, H, n_a, M):
     import torch
@@ -32,7 +32,7 @@ def test_selection_at_kernel_edges(cast_lib, dh, H, n_a, M):
                 assert got[i, h].tolist() == oracle.route.topk_select(want[i, h], topk), (i, h, topk)
 
 
-@pytest.mark.parametrize("M", [60, 200, 400, 600])
+@pytest.mark.parametrize("M", [20, 60, 200, 400, 600])
 def test_selection_with_infinite_scores(cast_lib, M):
     """Scores of +-inf order like any other value, ties among them by index."""
     import torch
