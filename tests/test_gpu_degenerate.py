@@ -116,7 +116,7 @@ def test_par_single_channel_and_adjacent_anchors(cast_lib):
 
 # ---- the largest sizes the boundary accepts
 def test_route_4096_chunks(cast_lib):
-    """M = 4096 chunks (the bitonic selection's whole LDS key array) with exact ties."""
+    """M = 4096 chunks (four per lane of the selection's 16 waves) with exact ties."""
     from test_gpu_parity import check_route
     dev = "cuda"
     torch.manual_seed(4096)

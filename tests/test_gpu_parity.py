@@ -121,9 +121,9 @@ def test_route_ties_and_budget(cast_lib):
 
 @pytest.mark.parametrize("M", [64, 65, 256, 257, 1000])
 def test_route_many_chunks(cast_lib, M):
-    """Chunk counts around the TopK's paths: rank counting (one wave per 64 chunks,
-    up to 256 chunks) and the bitonic sorts above; budgets below, at and above a
-    multiple of 64, with byte-identical duplicate chunks for exact ties."""
+    """Chunk counts around the TopK's paths (one key per lane up to 64 chunks, four to
+    256, eight to 512, 16 waves above); budgets below, at and above a multiple of 64,
+    with byte-identical duplicate chunks for exact ties."""
     torch.manual_seed(500 + M)
     dev = "cuda"
     n_a, S, H, dh, Bv = 2, 40, 3, 64, 24
@@ -136,9 +136,10 @@ def test_route_many_chunks(cast_lib, M):
 
 def test_route_workspace_reuse(cast_lib):
     """One workspace serves consecutive calls of different shapes (channel groups
-    of one, two or four heads, a partial last group; rank-count and bitonic
-    selection): each call must match a call on a fresh workspace bit for bit, so
-    nothing a call leaves in the workspace reaches the next one."""
+    of one, two or four heads, a partial last group; scores and selection in one
+    launch, and above 512 chunks in two, with the scores in the workspace): each call
+    must match a call on a fresh workspace bit for bit, so nothing a call leaves in
+    the workspace reaches the next one."""
     dev = "cuda"
     shapes = [  # n_a, S, H, dh, M, Bv, topk
         (3, 100, 12, 128, 16, 70, 4),
@@ -146,7 +147,11 @@ def test_route_workspace_reuse(cast_lib):
         (4, 50, 3, 32, 9, 31, 2),
         (1, 64, 6, 32, 256, 8, 30),
         (2, 40, 3, 64, 300, 12, 9),
+        (2, 40, 3, 64, 600, 12, 60),
         (3, 100, 12, 128, 16, 70, 4),
+        (5, 20, 2, 32, 1100, 6, 200),
+        (2, 33, 5, 64, 40, 17, 7),
+        (2, 40, 3, 64, 600, 12, 60),
     ]
     nb = max(cast_lib.cast_route_kv_workspace_bytes(*s[:6]) for s in shapes)
     ws = torch.full((nb,), 0x7f, dtype=torch.uint8, device=dev)
@@ -295,9 +300,9 @@ def test_attn_many_routed_chunks(cast_lib, Bv, k_eff, n0):
 
 @pytest.mark.parametrize("dh", [32, 64, 128])
 @pytest.mark.parametrize("n_a,S,H,M,Bv,k_eff,n0", [
-    (1, 300, 2, 30, 100, 24, 37),    # general copy mode, 2 pieces, ragged key and query tails
-    (2, 256, 3, 128, 64, 128, 0),    # aligned mode, 8 pieces
-    (1, 70, 2, 64, 72, 60, 0),       # fast mode, 4 pieces, ragged last key tile
+    (1, 300, 2, 30, 100, 24, 37),    # general copy mode, ragged key and query tails
+    (2, 256, 3, 128, 64, 128, 0),    # aligned mode
+    (1, 70, 2, 64, 72, 60, 0),       # fast mode, ragged last key tile
     (1, 320, 2, 40, 64, 40, 0),      # last Q tile of exactly two live waves, aligned mode
 ])
 def test_attn_key_split(cast_lib, dh, n_a, S, H, M, Bv, k_eff, n0):
@@ -447,24 +452,30 @@ def check_par(cast_lib, resid_np, anchors, *, accumulate=False, gate_mode=0, x0=
 
 def test_par_workspace_reuse_and_long_target_runs(cast_lib):
     """One workspace serves consecutive PAR calls of different shapes (the fused
-    8x8 launches with edge classes, a 4x4 tiling launched per class, several pairs,
-    long runs of targets between and beyond the anchors, a pair with no interior
-    frame).  Each call matches a call on a fresh workspace bit for bit and the
+    8x8 launches with edge classes, with the gate inside the reconstruction and, where
+    conf_out is asked for, in its own launch with the coefficients in the workspace; the
+    one launch of up to 64 channels, which leaves the workspace alone; a 4x4 tiling
+    launched per class; several pairs, long runs of targets between and beyond the
+    anchors, a pair with no interior frame).  Each call matches a call on a fresh workspace bit for bit and the
     oracle within the PAR bar."""
     dev = "cuda"
     rng = np.random.default_rng(77)
-    cases = [  # n_frames, Hg, Wg, D, anchors, tile, accumulate
-        (45, 13, 19, 64, (2, 40), 8, False),
-        (9, 16, 16, 96, (0, 3, 8), 4, True),
-        (40, 9, 10, 40, (5, 6, 30), 8, True),
-        (45, 13, 19, 64, (2, 40), 8, False),
+    cases = [  # n_frames, Hg, Wg, D, anchors, tile, accumulate, conf_out
+        (45, 13, 19, 130, (2, 40), 8, False, False),
+        (9, 16, 16, 96, (0, 3, 8), 4, True, False),
+        (40, 9, 10, 40, (5, 6, 30), 8, True, False),
+        (40, 9, 10, 96, (5, 6, 30), 8, True, False),
+        (21, 20, 13, 200, (1, 7, 18), 8, False, True),
+        (45, 13, 19, 64, (2, 40), 8, False, False),
+        (40, 9, 10, 96, (5, 6, 30), 8, True, True),
+        (45, 13, 19, 130, (2, 40), 8, False, False),
     ]
     nb = 0
-    for (n, hg, wg, d, anc, tile, acc) in cases:
+    for (n, hg, wg, d, anc, tile, acc, conf) in cases:
         prm = cast_lib.cast_par_params_default(tile_h=tile, tile_w=tile)
         nb = max(nb, cast_lib.cast_par_workspace_bytes(n, len(anc), hg, wg, d, prm))
     ws = torch.full((nb,), 0x7f, dtype=torch.uint8, device=dev)
-    for j, (n, hg, wg, d, anc, tile, acc) in enumerate(cases):
+    for j, (n, hg, wg, d, anc, tile, acc, conf) in enumerate(cases):
         base = rng.standard_normal((hg, wg, d))
         resid_np = np.zeros((n, hg, wg, d))
         for m, f in enumerate(anc):
@@ -475,7 +486,8 @@ def test_par_workspace_reuse_and_long_target_runs(cast_lib):
         outs = []
         for use_ws in (True, False):
             out = torch.from_numpy(x0.astype(np.float32)).to(dev)
-            cast_lib.cast_par_reconstruct(resid, anc, prm, out=out, workspace=ws if use_ws else None)
+            cf = torch.zeros(cast_lib.par_debug_shapes(len(anc), hg, wg, prm)[1], device=dev) if conf else None
+            cast_lib.cast_par_reconstruct(resid, anc, prm, out=out, conf_out=cf, workspace=ws if use_ws else None)
             torch.cuda.synchronize()
             outs.append(out)
         assert torch.equal(outs[0], outs[1]), j
@@ -497,7 +509,7 @@ def test_par_gate_inline_and_launched(cast_lib):
     dev = "cuda"
     rng = np.random.default_rng(21)
     for (n, Hg, Wg, D, anchors) in [(8, 30, 52, 192, (0, 3, 7)), (6, 13, 11, 70, (1, 4)),
-                                    (9, 16, 16, 64, (0, 2, 5, 8))]:
+                                    (9, 16, 16, 72, (0, 2, 5, 8))]:
         base = rng.standard_normal((Hg, Wg, D))
         resid = np.zeros((n, Hg, Wg, D))
         for j, a in enumerate(anchors):
