@@ -65,8 +65,8 @@ __device__ __forceinline__ void sum_tokens(const uint16_t* __restrict__ base, in
 // chunks; kMeansWaves / PACK waves share a segment, wave w of them summing tokens
 // [w T / n, (w + 1) T / n), and are added through LDS in wave order.
 // HBM-bound: 6.0 TB/s on 32 chunks of 3520 tokens (779 MB).  Short chunks leave
-// a wave one or two loads and the dispatcher one workgroup per 16 KB, so two chunks
-// share a workgroup (launch_pool_means has the line).
+// a wave one or two loads and the dispatcher one workgroup per 16 KB, so on long grids
+// two chunks share a workgroup (launch_pool_means has the line).
 template <int PACK>
 __global__ __launch_bounds__(kMeansWaves * 64) void route_means_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -239,12 +239,15 @@ cast_status_t launch_pool_means(const void* q, const void* k, const void* v, int
                                 int Bv, int D, float* means, hipStream_t stream) {
   const int n_chunks = v != nullptr ? 2 * M : M;
   const int groups = (D + kMeansCh - 1) / kMeansCh;
-  // Two chunks per workgroup where that was faster: chunks of 64 tokens on grids that
-  // one workgroup per chunk makes long (1764 segments x 24 groups: 156.7 -> 149.9 us a
-  // call; 393 x 12 groups 27.9 against 28.1) and shorter chunks on any grid (256 of 16
-  // tokens: 19.8 -> 15.5 us).  At 128 tokens it lost (512 x 24 groups: 71.4 -> 76.3).
+  // Two chunks per workgroup where that is faster: chunks of up to 64 tokens on grids that
+  // one workgroup per chunk makes longer than the chip holds at once (eight waves each,
+  // about 1024 to 2048 workgroups).  Device times of a routing call, one and two chunks per
+  // workgroup, by segments x groups: 64 tokens 1536 12.5 and 13.4 us, 2400 15.1 and 15.0,
+  // 3072 18.5 and 17.8, 12288 47.0 and 44.2, 42240 148 and 137; 16 tokens 1536 11.4 and
+  // 11.7; 33 tokens 2400 13.6 and 12.4, 12288 40.3 and 33.3.  Longer chunks lose at most
+  // sizes (96 tokens 4680 30.9 and 32.0, 128 tokens 24000 136 and 139).
   constexpr int P = 2;
-  const bool pack = Bv <= 32 || (Bv <= 64 && (long long)n_chunks * groups >= 16384);
+  const bool pack = Bv <= 64 && (long long)n_chunks * groups >= 2048;
   const int rows = n_a + (pack ? (n_chunks + P - 1) / P : n_chunks);
   hipLaunchKernelGGL((pack ? route_means_kernel<P> : route_means_kernel<1>), dim3(groups, rows),
                      dim3(kMeansWaves * 64), 0, stream, static_cast<const uint16_t*>(q),
