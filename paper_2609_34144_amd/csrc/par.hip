@@ -1,6 +1,8 @@
 // Phase-Aware Reconstruction on gfx950 (Sec. 4.3; App. A.2; eq:block).
 //
-// Three stream-ordered kernels per call:
+// Three stream-ordered kernels per call, two where the reconstruction blocks take the
+// gate themselves (grids the chip holds in one round), one up to 64 channels (par_one in
+// par_device.h):
 //   par_xspec  grid (tile, channel block of 64, anchor pair): every lane owns one
 //              channel of one tile, transforms both anchors in registers and
 //              writes its per-bin products F_b conj(F_a) and |F_b||F_a|; the 64
@@ -48,7 +50,12 @@ __global__ __launch_bounds__(64) void par_xspec_kernel(ParArgs a, TileClass k,
 
 constexpr int kGateTargets = 8;   // targets per gate block
 constexpr int kGateWaves = 4;     // waves per gate block
-constexpr int kInlineBlocksPerCU = 7;   // reconstruction blocks per compute unit up to which the gate is inline
+// Reconstruction blocks per compute unit up to which the gate is inline: what a compute
+// unit holds with it, seven by LDS in write mode (21 KB each), eight by registers in
+// accumulate mode (18 KB).  Launched and inline gate: accumulating 8 frames of 30x52x2112
+// (7.2 blocks) 56.1 and 53.3 us, of 30x52x2304 (7.9) 51.9 and 49.1, 5 of 64x64x2048 (8.0)
+// 63.5 and 62.5, 8 of 30x52x2432 (8.3) 57.5 and 58.8; writing 30x52x2112 41.8 and 46.3.
+constexpr int kInlineBlocksWrite = 7, kInlineBlocksAccumulate = 8;
 
 __global__ __launch_bounds__(64 * kGateWaves) void par_gate_kernel(ParArgs a,
                                                                     const float* __restrict__ partial,
@@ -310,10 +317,10 @@ cast_status_t launch_par(const float* resid, const int* anchors, int n_anchor, i
     hipLaunchKernelGGL(row.xspec[wi], grid, dim3(kChb), 0, stream, a, cs, resid, partial);
     st = check_launch("par_xspec");
     if (st != CAST_OK) return st;
-    // When the reconstruction grid fits in one round of resident blocks (kInlineBlocksPerCU
-    // per compute unit), each block computes its tile's gate itself, and the gate launch,
+    // When the reconstruction grid fits in one round of resident blocks, each block computes its tile's gate itself, and the gate launch,
     // a serial step of its own, goes; the debug outputs come from the gate launch.
-    const bool inl = !debug && (long long)grid.x <= (long long)kInlineBlocksPerCU * cus;
+    const bool inl = !debug && (long long)grid.x <=
+                                   (long long)(p.accumulate ? kInlineBlocksAccumulate : kInlineBlocksWrite) * cus;
     if (!inl) {
       hipLaunchKernelGGL(par_gate_kernel, gate_grid, dim3(64 * kGateWaves), 0, stream, a,
                          (const float*)partial, coef);
