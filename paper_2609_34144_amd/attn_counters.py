@@ -7,6 +7,9 @@
     python -m paper_2609_34144_amd.attn_counters --workload NAME --db D/run_results.db \
         --cmd "..." --out profiles/STEM
 
+NAME is a workload of bench.py, or an attention case of perf/cases.py whose passes the
+profiled program ran.
+
 Writes STEM.md: the per-dispatch averages of the counters for the attention
 kernel and what follows from them:
 
@@ -56,8 +59,13 @@ def summarize(workload: str, db: str, cmd: str, out_stem: str) -> dict:
         sys.path.insert(0, ROOT)
     import gen
     from bench import attn_flops
-    w = gen.get(workload)
-    algo = attn_flops(w, min(w.topk, w.M))
+    from perf import cases
+    case = {c["name"]: c for c in cases.listed()}.get(workload)
+    if case is not None:
+        algo = cases.work(case)["flops"]
+    else:
+        w = gen.get(workload)
+        algo = attn_flops(w, min(w.topk, w.M))
     v, dur_ns, n = per_dispatch(db)
     cyc = v["GRBM_GUI_ACTIVE"] / N_XCD
     d = {
@@ -76,7 +84,7 @@ def summarize(workload: str, db: str, cmd: str, out_stem: str) -> dict:
     }
     with open(out_stem + ".md", "w") as fh:
         fh.write(f"# Matrix-core counters of the routed attention, {workload}\n\n")
-        fh.write("One rocprofv3 counter pass over bench.py; averages per dispatch of "
+        fh.write("One rocprofv3 counter pass; averages per dispatch of "
                  f"`{KERNEL}` (counters summed over the chip).\n\nCommand:\n\n```\n{cmd}\n```\n\n")
         fh.write("| counter | per dispatch |\n|---|---|\n")
         for c in COUNTERS:

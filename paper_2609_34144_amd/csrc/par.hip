@@ -305,10 +305,11 @@ cast_status_t launch_par(const float* resid, const int* anchors, int n_anchor, i
     const int cus = device_cu_count();
     const bool debug = theta_out != nullptr || gate_out != nullptr || conf_out != nullptr;
     // Up to kChb channels one wave holds a (tile, pair) whole, and the three passes are
-    // one launch: 4 frames of 8x8x64 21.0 -> 16.8 us, 8 of 30x52x64 25.7 -> 21.0.  Several
-    // waves per (tile, pair) in one workgroup lost: 12 frames of 44x44x128 36.3 -> 37.5,
-    // 8 of 12x12x512 33.4 -> 53.2 us (the waves of a compute unit share its instruction
-    // cache, and each runs several thousand instructions of straight-line code once).
+    // one launch: accumulating with the anchor update, 4 frames of 8x8x64 21.0 -> 16.0 us
+    // a call, 8 of 30x52x64 24.7 -> 19.4.  Several waves per (tile, pair) in one workgroup
+    // lost: 12 frames of 44x44x128 36.3 -> 37.5, 8 of 12x12x512 33.4 -> 53.2 us (the waves
+    // of a compute unit share its instruction cache, and each runs several thousand
+    // instructions of straight-line code once).
     if (!debug && pl.n_chblk == 1) {
       hipLaunchKernelGGL((p.accumulate ? row.one_a[wi] : row.one_w[wi]), grid, dim3(kChb), 0, stream, a, cs,
                          resid, out);
@@ -317,8 +318,9 @@ cast_status_t launch_par(const float* resid, const int* anchors, int n_anchor, i
     hipLaunchKernelGGL(row.xspec[wi], grid, dim3(kChb), 0, stream, a, cs, resid, partial);
     st = check_launch("par_xspec");
     if (st != CAST_OK) return st;
-    // When the reconstruction grid fits in one round of resident blocks, each block computes its tile's gate itself, and the gate launch,
-    // a serial step of its own, goes; the debug outputs come from the gate launch.
+    // When the reconstruction grid fits in one round of resident blocks, each block computes
+    // its tile's gate itself, and the gate launch, a serial step of its own, goes; the debug
+    // outputs come from the gate launch.
     const bool inl = !debug && (long long)grid.x <=
                                    (long long)(p.accumulate ? kInlineBlocksAccumulate : kInlineBlocksWrite) * cus;
     if (!inl) {
@@ -327,7 +329,7 @@ cast_status_t launch_par(const float* resid, const int* anchors, int n_anchor, i
       st = check_launch("par_gate");
       if (st != CAST_OK) return st;
     }
-    // accumulate mode with several pairs: stream the targets (see recon_body)
+    // accumulate mode with several pairs: stream the targets (see recon_targets)
     const ReconFusedFn rf = !p.accumulate ? (inl ? row.inl_w[wi] : row.recon_w[wi])
                             : (pl.n_pairs > 1 ? (inl ? row.inl_as[wi] : row.recon_as[wi])
                                               : (inl ? row.inl_a[wi] : row.recon_a[wi]));
