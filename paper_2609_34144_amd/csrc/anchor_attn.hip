@@ -788,12 +788,13 @@ cast_status_t launch_dh(AttnArgs a, hipStream_t stream) {
 // Fewer left than compute units: as many pieces as an estimate finds soonest.  A piece
 // takes ceil(tiles / s) tile times (us per 64-key tile with one workgroup on a compute
 // unit, and with two); the split adds the merge launch, which walks the s pieces, and the
-// fp32 partials, cheap past the first 108 pieces of 256 x 128 (14 MB), dear again where
+// fp32 partials, cheaper past the first 108 pieces of 256 x 128 (14 MB), dear again where
 // they fill the L2s (256 pieces, 33.5 MB).  Behind whole rounds the launch is part hidden.
-// The constants are a fit to 5000 timed plans of 950 shapes (2 to 1584 units, 1 to 500
-// tiles): within 3% of the best plan timed on nine shapes in ten.  Those of long runs on
-// the full chip (1.65 us a tile at dh = 128) split too soon: 64 units of 14 tiles 27.2 us
-// whole and 31.3 so, of 48 tiles 41.3 in three pieces and 47.2 in four.
+// The constants are a fit to 5800 plans of 1040 shapes (2 to 1360 units, up to 485 tiles),
+// each timed over three sets of inputs in turn.  Those of long runs on the full chip (1.65
+// us a tile at dh = 128) split too soon: 64 units of 14 tiles 27.2 us whole and 31.3 so,
+// of 48 tiles 41.3 in three pieces and 47.2 in four; those of one set of inputs, whose
+// keys stay in the L2s, too late: 28 units of 12 tiles 23.6 us whole and 20.9 in three.
 //
 // More left than compute units (two workgroups each, dh <= 64): the pieces would not fit
 // beside each other, and left whole, the few units past one per compute unit hold the
@@ -818,13 +819,13 @@ AttnSplitPlan attn_split_plan(int n_a, int S, int H, int dh, long long L, int cu
     rem -= cus;
     best = reserve = std::min({8ll, cus / rem, nt_all / 16});
   } else {
-    const double tile_us[2] = {dh == 128 ? 1.08 : dh == 64 ? 1.06 : 0.82, dh == 64 ? 1.83 : 1.18};
+    const double tile_us[2] = {dh == 128 ? 1.07 : dh == 64 ? 1.03 : 0.84, dh == 64 ? 1.73 : 1.38};
     auto tiles_us = [&](double tiles, long long s) { return tiles * tile_us[rem * s > cus ? 1 : 0]; };
     auto split_us = [&](long long s) {
       if (s == 1) return 0.0;
       const double full = (double)(rem * s * dh) / 128;   // in pieces of 256 x 128
-      return (units > slots ? 0.3 : 2.1) + 0.38 * (double)s + 0.067 * std::min(full, 108.0) +
-             0.028 * std::max(full - 108.0, 0.0) + (full > 240 ? 3.3 : 0.0);
+      return (units > slots ? 2.3 : 3.3) + 0.43 * (double)s + 0.044 * std::min(full, 108.0) +
+             0.023 * std::max(full - 108.0, 0.0) + (full > 240 ? 2.4 : 0.0);
     };
     auto estimate = [&](long long s) { return tiles_us((double)((nt_all + s - 1) / s), s) + split_us(s); };
     for (long long s = 2; s <= kMaxSplit && rem * s <= slots && s * kMinPieceTiles <= nt_all; ++s) {
